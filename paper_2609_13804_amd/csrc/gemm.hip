@@ -4,9 +4,10 @@
 //
 // Accumulation is float32 and the result is stored once (bfloat16 rounded to
 // nearest-even, or float32).  Two cores:
-//  * bfloat16, gemm_bf16_256: 256 x 256 tiles of eight waves, each wave owning
-//    128 x 64 as 32 x 32 tiles of v_mfma_f32_32x32x16_bf16; K in 32-wide
-//    stages through a four-deep LDS ring filled straight from global memory.
+//  * bfloat16, gemm_bf16: 256 x 256 tiles of eight waves, each wave owning
+//    128 x 64 as 16 x 16 tiles of v_mfma_f32_16x16x32_bf16 (smaller tiles for
+//    small products and for the last round of a large one); K in 64-wide
+//    stages through LDS rings filled straight from global memory.
 //  * float32, gemm_block: BM x BN tiles of four waves, each owning a
 //    (BM/2) x (BN/2) quadrant of 32 x 32 tiles of v_mfma_f32_32x32x2_f32; K in
 //    BK-wide stages through two LDS buffers, the next stage fetched into
@@ -28,6 +29,7 @@ namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
@@ -167,246 +169,275 @@ __device__ __forceinline__ void gemm_block(const ARows& ar, const BRows& br, int
     }
 }
 
-// ------------------------------------------------------------------ bf16, 256 x 256 tiles
+// ------------------------------------------------------------------ bf16
 //
-// Large bfloat16 GEMMs: a 256 x 256 output tile per workgroup of four or
-// eight waves (MFMA 32x32x16 tiles, accumulators in AGPRs), K in 32-wide
-// stages.  Operand tiles go straight from global memory into LDS
-// (global_load_lds_dwordx4: one wave instruction fills 1 KiB = 16 rows x 64
-// bytes) through a ring of S stage buffers, loads running S - 1 stages ahead
-// of the matrix cores.  Each stage's loads are issued a few at a time between
-// matrix-core instructions rather than in one burst.  Within a 64-byte row
-// the four 16-byte chunks are stored XOR-swizzled (chunk c of row r at slot
-// c ^ ((r >> 2) & 3)), which the load realises by choosing each lane's source
-// address: a 16-byte fragment read serves 16 lanes (16 consecutive rows, 4 rows
-// per 256-byte pass over the 64 banks) at a time, and rows 4 apart take
-// different slots, so no two lanes of a pass share a bank.  Rows past M (N)
-// are clamped to the last valid row and their results are not stored.
-constexpr int kBM = 256, kBN = 256, kBK = 32, kStages = 4;
-constexpr int kOpBytes = kBM * kBK * 2;                // one operand tile, 16 KiB
-constexpr int kStageBytes = 2 * kOpBytes;              // A and B, 32 KiB
+// The bfloat16 core: a BM x BN output tile per workgroup of WGM x WGN waves,
+// K in 64-wide stages.  Operand tiles go straight from global memory into LDS
+// (global_load_lds_dwordx4: one wave instruction fills 1 KiB = 8 rows x 128
+// bytes), the A tiles through a ring of D + 1 buffers and the B tiles through a
+// ring of D, loads running up to D stages ahead of the matrix cores.
+//
+// What bounds it and why this shape (9216 x 4096 x 16384 product; one card):
+//  * the operand stream into a CU.  Measured without matrix work, the tiles of
+//    such a product stream at 13 TB/s in 64-byte row pieces and at 14.8 TB/s in
+//    128-byte ones (whole cache lines; 16 against 23 TB/s when they hit the L2),
+//    so a stage is 64 wide;
+//  * power.  With normally distributed operands in registers the matrix cores
+//    sustain 1.79 PFLOP/s with the 32x32x16 instruction and 2.07 with 16x16x32
+//    (2.45 with zeros): half the accumulator traffic per flop;
+//  * barriers: one per stage, in its middle (below).
+// A core of 32-wide stages and 32x32x16 instructions took 1001 us (1.24 PFLOP/s)
+// where this one takes 864 (1.43), with bit-identical results; on 8192 x 8192 x
+// 4096 444 against 378 us.
+//
+// A 128-byte row holds eight 16-byte chunks, chunk c of row r at slot
+// c ^ ((r >> 1) & 7), which the load realises by choosing each lane's source
+// address: a 16-lane pass of a fragment read (16 consecutive rows, one chunk
+// column) then touches every bank once.  Rows past M (N) are clamped to the
+// last valid row and their results are not stored.
+//
+// The product is formed transposed (B as the instruction's row operand), so a
+// lane holds four consecutive columns of one row and the tile is staged through
+// LDS in 8-byte (bfloat16) or 16-byte (float32) pieces.
+constexpr int kKStage = 64;                // K of one stage
+constexpr int kRowBytes = 2 * kKStage;     // one staged operand row
 
-// Byte offset of (row, 16-byte chunk) in a swizzled operand tile (64-byte rows).
-__device__ __forceinline__ int swz(int row, int chunk) {
-  return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4);
-}
+template <int BM_, int BN_, int WGM_, int WGN_, int D_>
+struct BfTile {
+  static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, D = D_;
+  static constexpr int WAVES = WGM * WGN, THREADS = 64 * WAVES;
+  static constexpr int BUFA = BM * kRowBytes, BUFB = BN * kRowBytes;
+  static constexpr int OFFB = (D + 1) * BUFA;               // B ring after the A ring
+  static constexpr int LDS = OFFB + D * BUFB;
+  static constexpr int TM = BM / WGM / 16, TN = BN / WGN / 16;   // 16 x 16 tiles of a wave
+  static constexpr int LA = BM / 8 / WAVES, LB = BN / 8 / WAVES; // loads per wave and stage
+  static_assert(BM % (8 * WAVES) == 0 && BN % (8 * WAVES) == 0, "whole loads per wave");
+  static_assert(WAVES % 2 == 0, "the parity of a wave's row groups is the wave's");
+  static_assert(LDS <= kLdsBytes, "the rings fit the LDS");
+};
+using TileWhole = BfTile<256, 256, 2, 4, 2>;     // 160 KB
+using TileHalf = BfTile<256, 128, 2, 4, 2>;      // 128 KB
+using TileQuarter = BfTile<128, 128, 2, 4, 4>;   // 144 KB
+using TileSmall = BfTile<64, 64, 2, 2, 4>;       // 72 KB: two workgroups a CU
 
-// WAVES = 4: each wave owns a 128 x 128 quadrant (one wave per SIMD).
-// WAVES = 8: each wave owns 128 x 64 (two waves per SIMD, so one wave's
-// matrix-core work covers the other's waits at barriers and loads).
 // Output epilogue of the bfloat16 core: the product as it is, or (bfloat16
 // output only) the product rounded to bfloat16, plus a per-column float32 bias,
 // optionally through the exact GELU, rounded again: the same values as storing
 // the product and then running a bias (+ GELU) pass over it.
 constexpr int kEpiNone = 0, kEpiBias = 1, kEpiBiasGelu = 2;
 
-template <int WAVES, typename OutT, class ARows, class BRows, int EPI = kEpiNone>
-__device__ __forceinline__ void gemm_bf16_256(const ARows& ar, const BRows& br, int64_t M,
-                                              int64_t N, int K, OutT* __restrict__ C, int64_t ldc,
-                                              int64_t m0, int64_t n0, char* smem,
-                                              const float* __restrict__ bias = nullptr) {
-  static_assert(WAVES == 4 || WAVES == 8, "four or eight waves");
+template <class G, typename OutT, class ARows, class BRows, int EPI = kEpiNone>
+__device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int64_t M, int64_t N,
+                                          int K, OutT* __restrict__ C, int64_t ldc, int64_t m0,
+                                          int64_t n0, char* smem,
+                                          const float* __restrict__ bias = nullptr) {
   static_assert(EPI == kEpiNone || sizeof(OutT) == 2, "bias epilogues write bfloat16");
-  constexpr int GPW = 16 / WAVES;            // 16-row groups per operand per wave
-  constexpr int LPW = 2 * GPW;               // DMA instructions per wave per stage
-  constexpr int WGN = WAVES / 2;             // waves along N (two along M)
-  constexpr int TN = 8 / WGN;                // 32-column MFMA tiles per wave along N
+  constexpr int D = G::D, LA = G::LA, LB = G::LB, TM = G::TM, TN = G::TN, W = G::WAVES;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int wm = wave / WGN, wn = wave % WGN;
+  const int wm = wave / G::WGN, wn = wave % G::WGN;
 
-  // This wave loads 16-row groups wave + WAVES i (i < GPW) of both operand
-  // tiles; lane (rl = lane / 4, slot = lane % 4) fetches chunk
-  // slot ^ ((rl >> 2) & 3) of row rl.
-  const int rl = lane >> 2;
-  const int chunk = (lane & 3) ^ ((rl >> 2) & 3);
-  const __bf16* pa[GPW];
-  const __bf16* pb[GPW];
+  // This wave loads 8-row groups wave + W q of both operand tiles; lane
+  // (row lane / 8, slot lane % 8) fetches the chunk that the swizzle puts there.
+  const int dchunk = (lane & 7) ^ (((wave & 1) << 2) + (lane >> 4));
+  typename ARows::Src sa[LA];
+  typename BRows::Src sb[LB];
 #pragma unroll
-  for (int i = 0; i < GPW; ++i) {
-    const int r = 16 * (wave + WAVES * i) + rl;
-    const int64_t gm = m0 + r < M ? m0 + r : M - 1;
-    const int64_t gn = n0 + r < N ? n0 + r : N - 1;
-    pa[i] = ar.row(gm) + chunk * 8;
-    pb[i] = br.row(gn) + chunk * 8;
-  }
-  auto issue = [&](int buf, int k0) {
-    char* a = smem + buf * kStageBytes;
-    char* b = a + kOpBytes;
+  for (int q = 0; q < LA; ++q) sa[q] = ar.src(m0, 8 * (wave + W * q) + (lane >> 3), M, dchunk * 8);
 #pragma unroll
-    for (int i = 0; i < GPW; ++i) lds_dma16(pa[i] + k0, a + (wave + WAVES * i) * 1024);
-#pragma unroll
-    for (int i = 0; i < GPW; ++i) lds_dma16(pb[i] + k0, b + (wave + WAVES * i) * 1024);
+  for (int q = 0; q < LB; ++q) sb[q] = br.src(n0, 8 * (wave + W * q) + (lane >> 3), N, dchunk * 8);
+  const typename ARows::Base abase = ar.base_of(m0);
+  const typename BRows::Base bbase = br.base_of(n0);
+  auto issue_a = [&](int kt, int q, int slot) {
+    ARows::dma(abase, sa[q], kt * kKStage, smem + slot * G::BUFA + (wave + W * q) * 1024);
+  };
+  auto issue_b = [&](int kt, int q, int slot) {
+    BRows::dma(bbase, sb[q], kt * kKStage, smem + G::OFFB + slot * G::BUFB + (wave + W * q) * 1024);
   };
 
-  f32x16_t acc[4][TN];
+  f32x4_t acc[TM][TN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  const int arow0 = wm * 128 + (lane & 31);
-  const int brow0 = wn * (32 * TN) + (lane & 31);
-  const int khalf = lane >> 5;
-  auto load_frags = [&](const char* As, const char* Bs, int ks, bf16x8_t (&a)[4], bf16x8_t (&b)[TN]) {
-    const int c = ks * 2 + khalf;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const bf16x8_t*>(As + swz(arow0 + 32 * i, c));
-#pragma unroll
-    for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const bf16x8_t*>(Bs + swz(brow0 + 32 * j, c));
+  // Fragment of 16 rows at k-step ks (32 wide): lane l reads chunk 4 ks + l / 16
+  // of row l % 16, whose slot bits do not depend on the 16-row group.
+  const int l16 = lane & 15, lk = lane >> 4;
+  const int slot0 = (lk ^ (l16 >> 1)) << 4;
+  const int aoff = (wm * (G::BM / G::WGM) + l16) * kRowBytes + slot0;
+  const int boff = G::OFFB + (wn * (G::BN / G::WGN) + l16) * kRowBytes + slot0;
+  auto frag = [&](int buf, int off, int ks, int i) {
+    return *reinterpret_cast<const bf16x8_t*>(smem + buf + (off ^ (ks << 6)) + i * 16 * kRowBytes);
   };
+  struct Frags {
+    bf16x8_t a[TM], b[TN];
+  };
+  Frags f0, f1;                            // k-step 0 and 1 of a stage
 
-  // Software pipeline over K stages.  Iteration kt multiplies stage kt in two
-  // halves (16 k each); between them it waits for stage kt + 1, passes the
-  // workgroup barrier, refills the ring with stage kt + S - 1 and starts
-  // reading stage kt + 1's fragments, so the barrier and the LDS latency hide
-  // behind matrix-core work.
-  const int KT = K / kBK;
+  // A stage is two phases of TM x TN matrix instructions: k-step 0 (f0), while
+  // k-step 1's fragments (f1) are read, then k-step 1, while the next stage's
+  // first fragments are read into f0.  Between the phases every wave has read
+  // all of stage kt, and passes the workgroup barrier after waiting for its own
+  // loads of stage kt + 1: that one barrier both publishes stage kt + 1 and
+  // frees the buffers of stage kt.  Phase 0 issues the loads of A for stage
+  // kt + D (into the buffer of stage kt - 1), phase 1 those of B (into the
+  // buffer just freed), a few at a time between the matrix instructions.
+  const int KT = K / kKStage;
 #pragma unroll
-  for (int s = 0; s < kStages - 1; ++s)
-    if (s < KT) issue(s, s * kBK);
-  if (KT > kStages - 2) wait_vmcnt<(kStages - 2) * LPW>();
+  for (int s = 0; s < D; ++s)
+    if (s < KT) {
+#pragma unroll
+      for (int q = 0; q < LA; ++q) issue_a(s, q, s);
+#pragma unroll
+      for (int q = 0; q < LB; ++q) issue_b(s, q, s);
+    }
+  if (KT >= D) wait_vmcnt<(D - 1) * (LA + LB)>();
   else wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  // Two fragment sets used in turn (the loop is unrolled by two), so the
-  // next stage's fragments land in registers no copy has to wait for.
-  struct Frags {
-    bf16x8_t a0[4], b0[TN], a1[4], b1[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) f0.b[j] = frag(0, boff, 0, j);
+#pragma unroll
+  for (int i = 0; i < TM; ++i) f0.a[i] = frag(0, aoff, 0, i);
+
+  // One phase: matrix instructions on `cur` in TM groups; the first groups also
+  // read `nxt` (two or three fragments each), and load(i) issues group i's loads.
+  auto phase = [&](Frags& cur, Frags& nxt, bool read, int abuf, int bbuf, int ks, auto&& load) {
+    constexpr int R = TM + TN, GR = TM > 2 ? TM - 2 : TM, PER = (R + GR - 1) / GR;
+    __builtin_amdgcn_s_setprio(1);   // the wave whose operands are ready goes first
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.b[j], cur.a[i], acc[i][j], 0, 0, 0);
+      if (read) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+          const int r = i * PER + u;
+          if (r < TN) nxt.b[r] = frag(bbuf, boff, ks, r);
+          else if (r < R) nxt.a[r - TN] = frag(abuf, aoff, ks, r - TN);
+        }
+      }
+      load(i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_s_setprio(0);
   };
-  Frags f0, f1;
-  load_frags(smem, smem + kOpBytes, 0, f0.a0, f0.b0);
-  load_frags(smem, smem + kOpBytes, 1, f0.a1, f0.b1);
-  // DMA instruction q of a stage: the first GPW fill A's row groups, the rest B's.
-  auto issue_one = [&](int buf, int k0, int q) {
-    char* a = smem + buf * kStageBytes;
-    if (q < GPW) lds_dma16(pa[q] + k0, a + (wave + WAVES * q) * 1024);
-    else lds_dma16(pb[q - GPW] + k0, a + kOpBytes + (wave + WAVES * (q - GPW)) * 1024);
-  };
+  int ia = 0, ib = 0;                      // ring slots of stage kt
   // MORE / REFILL: 1 means always, -1 decided at run time.  The steady-state
   // loop instantiates both as 1, so its body has no branches: at a join of
   // branches the compiler's wait counting falls back to waiting for every
-  // outstanding LDS read, and each half-step would then stall on the
-  // fragment reads it has just issued.
-  auto step = [&](int kt, Frags& cur, Frags& nxt, auto more_c, auto refill_c) {
+  // outstanding LDS read.
+  auto stage = [&](int kt, auto more_c, auto refill_c) {
     constexpr int MORE = decltype(more_c)::value, REFILL = decltype(refill_c)::value;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.a0[i], cur.b0[j], acc[i][j], 0, 0, 0);
     const bool more = MORE == 1 || kt + 1 < KT;
-    const bool refill = REFILL == 1 || kt + kStages - 1 < KT;
-    if (more) {
-      // Stage kt + 1 has landed once at most (stages issued after it) x loads
-      // of this wave remain.  The buffer refilled below held stage kt - 1,
-      // whose fragments every wave consumed before this barrier.
-      if (refill) wait_vmcnt<(kStages - 3) * LPW>();
-      else wait_vmcnt<0>();
-      // Bare s_barrier (no fence): a workgroup fence would wait for every load
-      // still in flight and collapse the ring to a single stage.
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      const char* As = smem + ((kt + 1) % kStages) * kStageBytes;
-      load_frags(As, As + kOpBytes, 0, nxt.a0, nxt.b0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    // The refill of stage kt + S - 1 is spread over this half's matrix-core
-    // work: issued in one burst, the loads would stall this wave's issue until
-    // the memory pipeline drained them, and the matrix cores with it.
-    const int rbuf = (kt + kStages - 1) % kStages, rk0 = (kt + kStages - 1) * kBK;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.a1[i], cur.b1[j], acc[i][j], 0, 0, 0);
+    const bool refill = REFILL == 1 || kt + D < KT;
+    const int ra = ia == 0 ? D : ia - 1, rb = ib;          // slots of A and B of stage kt + D
+    const int ia2 = ia == D ? 0 : ia + 1, ib2 = ib == D - 1 ? 0 : ib + 1;
+    phase(f0, f1, true, ia * G::BUFA, ib * G::BUFB, 1, [&](int i) {
       if (refill) {
 #pragma unroll
-        for (int u = 0; u < LPW / 4; ++u) issue_one(rbuf, rk0, i * (LPW / 4) + u);
+        for (int q = 0; q < LA; ++q)
+          if (q * TM / LA == i) issue_a(kt + D, q, ra);
       }
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    });
     if (more) {
-      const char* As = smem + ((kt + 1) % kStages) * kStageBytes;
-      load_frags(As, As + kOpBytes, 1, nxt.a1, nxt.b1);
+      // Stage kt + 1 has landed once only loads issued after it remain: A of
+      // stages kt + 2 .. kt + D and B of stages kt + 2 .. kt + D - 1.
+      if (refill) wait_vmcnt<(D - 1) * LA + (D - 2) * LB>();
+      else wait_vmcnt<0>();
+      wait_lgkm0();                        // this wave's reads of stage kt
+      // Bare s_barrier (no fence): a workgroup fence would wait for every load
+      // still in flight and collapse the rings to a single stage.
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
     }
-    __builtin_amdgcn_sched_barrier(0);
+    phase(f1, f0, more, ia2 * G::BUFA, ib2 * G::BUFB, 0, [&](int i) {
+      if (refill) {
+#pragma unroll
+        for (int q = 0; q < LB; ++q)
+          if (q * TM / LB == i) issue_b(kt + D, q, rb);
+      }
+    });
+    ia = ia2;
+    ib = ib2;
   };
   using Always = std::integral_constant<int, 1>;
   using Checked = std::integral_constant<int, -1>;
   int kt = 0;
-  // Steady state: both steps of a pair have a next stage and a refill.
-  for (; kt + kStages < KT; kt += 2) {
-    step(kt, f0, f1, Always{}, Always{});
-    step(kt + 1, f1, f0, Always{}, Always{});
-  }
-  for (; kt + 1 < KT; kt += 2) {
-    step(kt, f0, f1, Checked{}, Checked{});
-    step(kt + 1, f1, f0, Checked{}, Checked{});
-  }
-  if (kt < KT) step(kt, f0, f1, Checked{}, Checked{});
+  for (; kt + D < KT; ++kt) stage(kt, Always{}, Always{});
+  for (; kt < KT; ++kt) stage(kt, Checked{}, Checked{});
 
-  // Epilogue through LDS: once every wave is past the K loop the operand ring
-  // is free, so the tile is staged there in row-major order and leaves as
-  // 16-byte row chunks (whole cache lines, an eighth or a quarter of the store
-  // instructions of storing the MFMA layout directly).  A float32 tile needs
-  // twice the ring, so it is staged in two passes of 128 rows (the waves with
-  // wm = 0, then wm = 1).  Chunks of rows with bit 2 set are XOR-ed by half a
-  // row of banks: the two rows one write instruction covers (r and r + 4)
-  // then hit different banks.
+  // Epilogue through LDS: once every wave is past the K loop the rings are
+  // free, so the tile is staged there in row-major order and leaves as 16-byte
+  // row chunks (whole cache lines).  A float32 tile may need several passes of
+  // ROWS rows.  Chunks of a row are XOR-ed by the row's index among the rows
+  // that share its banks, so the 16 rows that one staging write covers use
+  // different banks.
   constexpr int E = (int)sizeof(OutT);
   constexpr int EPC = 16 / E;                              // elements per 16-byte chunk
-  constexpr int CPR = kBN / EPC;                           // chunks per staged row
-  constexpr int ROWS = kStages * kStageBytes / (kBN * E);  // rows staged per pass
-  constexpr int PASSES = kBM / ROWS;
-  constexpr int XS = CPR / 8;
-  constexpr int THREADS = 64 * WAVES;
-  static_assert(ROWS == 128 || ROWS == 256, "one or two staging passes");
-  static_assert(ROWS * CPR % THREADS == 0, "whole chunks per thread");
-  auto sw = [](int lr) { return ((lr >> 2) & 1) * XS; };
+  constexpr int CPR = G::BN / EPC;                         // chunks per staged row
+  constexpr int FIT = G::LDS / (G::BN * E);
+  constexpr int ROWS = FIT >= G::BM ? G::BM : G::BM / 2;   // rows staged per pass
+  constexpr int PASSES = G::BM / ROWS;
+  constexpr int RPB = G::BN * E >= 256 ? 1 : 256 / (G::BN * E);   // rows per 256 bytes (64 banks)
+  constexpr int XM = CPR < 16 ? CPR - 1 : 15;
+  static_assert(ROWS <= FIT && ROWS * CPR % G::THREADS == 0, "whole chunks per thread");
+  static_assert(PASSES == 1 || (G::WGM == 2 && PASSES == 2), "a pass stages whole waves");
+  auto sw = [](int lr) { return (lr / RPB) & XM; };
   const bool vec = ((uintptr_t)C % 16 == 0) && ((int64_t)ldc * E % 16 == 0);
-  OutT* T = reinterpret_cast<OutT*>(smem);
   __syncthreads();
 #pragma unroll
   for (int p = 0; p < PASSES; ++p) {
     if (PASSES == 1 || wm == p) {
-      // 32x32 MFMA result layout: lane l, register r holds
-      // row 8*(r/4) + 4*(l/32) + r%4, column l%32.
-      float bj[TN];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int64_t col = n0 + wn * (32 * TN) + j * 32 + (lane & 31);
-        bj[j] = EPI != kEpiNone && col < N ? bias[col] : 0.0f;
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
+      // 16 x 16 MFMA result layout, operands exchanged: lane l, register r
+      // holds row l % 16, column 4 (l / 16) + r.
+      f32x4_t bj[TN];
+      if constexpr (EPI != kEpiNone) {
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int lr = wm * 128 - p * ROWS + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            const int lc = wn * (32 * TN) + j * 32 + (lane & 31);
-            OutT v;
-            if constexpr (EPI == kEpiNone) {
-              v = store_cvt<OutT>(acc[i][j][r]);
-            } else {
-              float y = __uint_as_float((uint32_t)f32_to_bf16_rne(acc[i][j][r]) << 16) + bj[j];
-              if constexpr (EPI == kEpiBiasGelu) y = 0.5f * y * (1.0f + erff(y * 0.70710678118654752f));
-              v = f32_to_bf16_rne(y);
-            }
-            T[lr * kBN + ((lc / EPC) ^ sw(lr)) * EPC + lc % EPC] = v;
+          for (int r = 0; r < 4; ++r) {
+            const int64_t col = n0 + wn * (G::BN / G::WGN) + 16 * j + 4 * lk + r;
+            bj[j][r] = col < N ? bias[col] : 0.0f;
           }
+      }
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int lr = wm * (G::BM / G::WGM) - p * ROWS + 16 * i + l16;
+        char* row = smem + lr * (G::BN * E);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const int lc = wn * (G::BN / G::WGN) + 16 * j + 4 * lk;
+          if constexpr (E == 2) {
+            uint16_t v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              if constexpr (EPI == kEpiNone) {
+                v[r] = f32_to_bf16_rne(acc[i][j][r]);
+              } else {
+                float y = __uint_as_float((uint32_t)f32_to_bf16_rne(acc[i][j][r]) << 16) + bj[j][r];
+                if constexpr (EPI == kEpiBiasGelu) y = 0.5f * y * (1.0f + erff(y * 0.70710678118654752f));
+                v[r] = f32_to_bf16_rne(y);
+              }
+            }
+            *reinterpret_cast<uint2*>(row + (((lc >> 3) ^ sw(lr)) << 4) + ((lc & 4) << 1)) =
+                make_uint2((uint32_t)v[0] | ((uint32_t)v[1] << 16), (uint32_t)v[2] | ((uint32_t)v[3] << 16));
+          } else {
+            *reinterpret_cast<f32x4_t*>(row + (((lc >> 2) ^ sw(lr)) << 4)) = acc[i][j];
+          }
+        }
+      }
     }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < ROWS * CPR / THREADS; ++q) {
-      const int c = tid + THREADS * q, lr = c / CPR, ch = c % CPR;
+    for (int q = 0; q < ROWS * CPR / G::THREADS; ++q) {
+      const int c = tid + G::THREADS * q, lr = c / CPR, ch = c % CPR;
       const int64_t row = m0 + p * ROWS + lr, col = n0 + (int64_t)ch * EPC;
       if (row >= M || col >= N) continue;
-      const OutT* src = T + lr * kBN + (ch ^ sw(lr)) * EPC;
+      const OutT* src = reinterpret_cast<const OutT*>(smem + lr * (G::BN * E) + ((ch ^ sw(lr)) << 4));
       OutT* dst = C + row * ldc + col;
       if (vec && col + EPC <= N) {
         *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
@@ -418,29 +449,89 @@ __device__ __forceinline__ void gemm_bf16_256(const ARows& ar, const BRows& br, 
   }
 }
 
+// How a product of T tiles of 256 x 256 is cut.  The first `full` tiles (whole
+// rounds of the 256 CUs) run as they are; the R left over would keep only R
+// CUs busy for a whole tile's time, so they are cut into `sub` parts when that
+// shortens the last round: four 128 x 128 parts up to 64 tiles, two 256 x 128
+// parts up to 128.  A round of whole tiles takes 1, of halves about 0.6 and of
+// quarters about 0.36 of a tile's time (K 4096: 88, 54 and 32 us), so beyond
+// 128 tiles two rounds of halves or three of quarters would take longer than
+// the whole tiles.  Measured, 9216 x 4096 x 4096 (576 tiles): 271 us whole, 243
+// halves, 234 quarters; 1037 x 3072 x 3584 (60 tiles): 67, 42, 30 us.
+// Products of up to 20 tiles, which quarters leave most CUs without work, take
+// 64 x 64 tiles, two workgroups a CU: 1077 x 1024 x 1024 8.5 against 10.3 us,
+// 1077 x 1024 x 4096 24 against 28 us.  Every element accumulates K in the same
+// order whatever the cut, so results do not depend on it.
+struct Cut {
+  int64_t full;        // whole tiles
+  int64_t blocks;      // workgroups
+  int sub;             // parts of each tile left over: 1, 2, 4, or 16 (64 x 64)
+};
+inline int64_t small_blocks(int64_t T) { return (T * 16 + 7) / 8 * 8; }   // all in 64 x 64
+inline Cut cut_tiles(int64_t T) {
+  constexpr int64_t kRound = 256;
+  Cut c;
+  c.full = T / kRound * kRound;
+  const int64_t R = T - c.full;
+  c.sub = T <= 20 ? 16 : R <= 64 ? 4 : R <= 128 ? 2 : 1;
+  c.blocks = c.full + (R * c.sub + 7) / 8 * 8;
+  return c;
+}
+
 // Workgroup w runs on XCD w % 8, which takes a contiguous run of the tiles in
 // banded order: bands of kBand row panels, each band walked column by column
 // (the last band as tall as the rows left).  The 32 tiles one XCD runs at a
 // time then cover about kBand row panels and 32 / kBand column panels, so they
 // share about 12 operand panels in that XCD's L2 (a row-major run of 32 tiles
-// spans all the column panels of a wide product).  Returns -1 for the padding
-// workgroups of the last run.
+// spans all the column panels of a wide product).
 constexpr int64_t kBand = 4;
 
-__device__ __forceinline__ int64_t xcd_tile(int64_t w, int64_t mt, int64_t nt) {
-  const int64_t tiles = mt * nt;
-  const int64_t per = (tiles + 7) / 8;
-  const int64_t i = (w % 8) * per + w / 8;
-  if (i >= tiles) return -1;
+// First row and column of tile i of an mt x nt grid in banded order.
+__device__ __forceinline__ void banded_tile(int64_t i, int64_t mt, int64_t nt, int64_t& m0, int64_t& n0) {
   const int64_t band = i / (kBand * nt), o = i % (kBand * nt);
   const int64_t rows = mt - band * kBand < kBand ? mt - band * kBand : kBand;
-  return (band * kBand + o % rows) * nt + o / rows;
+  m0 = (band * kBand + o % rows) * 256;
+  n0 = (o / rows) * 256;
+}
+
+// The tile (of T) and part that workgroup w takes under a cut (cut_tiles); the
+// whole tiles come first.  False for the padding workgroups.
+__device__ __forceinline__ bool cut_place(int64_t w, int64_t T, int64_t full, int sub, int64_t& tile,
+                                          int& part, bool& whole) {
+  whole = w < full || sub == 1;
+  part = 0;
+  if (w < full) {
+    tile = (w % 8) * (full / 8) + w / 8;
+    return true;
+  }
+  const int64_t v = w - full, parts = (T - full) * sub, per = (parts + 7) / 8;
+  const int64_t i = (v % 8) * per + v / 8;
+  if (i >= parts || v / 8 >= per) return false;
+  tile = full + i / sub;
+  part = (int)(i % sub);
+  return true;
 }
 
 // ------------------------------------------------------------------ row maps
 
+// The bfloat16 core takes an operand's rows through src(r0, r, R, c): where lane
+// row r of the tile starting at row r0 begins (column c; rows past the last of R
+// read the last), and dma(base, src, k, dst), its 16-byte load at column k + c.
+// Rows anywhere in memory keep a 64-bit address a lane:
+template <class Map>
+struct AnyRows {
+  struct Base {};
+  typedef const __bf16* Src;
+  __device__ Base base_of(int64_t) const { return {}; }
+  __device__ Src src(int64_t r0, int r, int64_t R, int c) const {
+    const int64_t g = r0 + r;
+    return static_cast<const Map*>(this)->row(g < R ? g : R - 1) + c;
+  }
+  __device__ static void dma(Base, Src s, int k, char* dst) { lds_dma16(s + k, dst); }
+};
+
 template <typename T>
-struct ProjRows {
+struct ProjRows : AnyRows<ProjRows<T>> {
   const T* X;
   int64_t T_vis;
   const T* s_start;
@@ -457,13 +548,38 @@ struct DenseRows {
   const T* base;
   int64_t ld;
   __device__ const T* row(int64_t m) const { return base + m * ld; }
+  // bfloat16 core: the tile's first row (uniform) and a 32-bit byte offset a
+  // lane, half the address registers (ld up to kMaxDenseLd)
+  typedef const char* Base;
+  typedef uint32_t Src;
+  __device__ Base base_of(int64_t r0) const {
+    const uint64_t p = (uint64_t)(base + r0 * ld);         // the same in every lane: into scalar registers
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
+    return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
+  }
+  __device__ Src src(int64_t r0, int r, int64_t R, int c) const {
+    const int64_t last = R - 1 - r0;
+    return (uint32_t)((r < last ? r : last) * ld + c) * (uint32_t)sizeof(T);
+  }
+  __device__ static void dma(Base b, Src s, int k, char* dst) { lds_dma16(b + (int64_t)k * sizeof(T), s, dst); }
+};
+
+// 255 rows of this many bfloat16 values stay within DenseRows' 32-bit byte
+// offsets; wider operands take the 64 x 64 tiles with whole addresses.
+constexpr int64_t kMaxDenseLd = 1 << 22;
+
+struct WideRows : AnyRows<WideRows> {
+  const __bf16* base;
+  int64_t ld;
+  __device__ const __bf16* row(int64_t m) const { return base + m * ld; }
 };
 
 // Gram operand rows of one group with tokens [g0, g0 + n): A side is
 // [Q tokens; q_start; V tokens; v_start; c_hi; c_mid; c_lo] (the last three
 // from the image's context split), B side is [K tokens; k_stop; k_start].
 template <typename T>
-struct GramARows {
+struct GramARows : AnyRows<GramARows<T>> {
   const T* KQV;
   int64_t g0, n, start_row;
   int h;
@@ -479,7 +595,7 @@ struct GramARows {
 };
 
 template <typename T>
-struct GramBRows {
+struct GramBRows : AnyRows<GramBRows<T>> {
   const T* KQV;
   int64_t g0, n, start_row;
   int h;
@@ -503,43 +619,124 @@ __global__ __launch_bounds__(kThreads) void project_gemm_kernel(ProjRows<T> ar, 
   gemm_block<T, OutT, BM, BN, BK>(ar, br, M, N, K, C, N, (t / nt) * BM, (t % nt) * BN, smem);
 }
 
-constexpr int kProjWaves = 8;
+constexpr int kBfThreads = TileWhole::THREADS;
+static_assert(TileHalf::THREADS == kBfThreads && TileQuarter::THREADS == kBfThreads, "one kernel runs all three");
 
-// Blocks [0, proj_blocks) take the projection's tiles in XCD-grouped order
-// (bfloat16 output); the blocks after them take the text projection's tiles
-// (float32 output).  The text tiles are dispatched last, onto the compute
-// units the projection's last round leaves idle.
-__global__ __launch_bounds__(64 * kProjWaves) void project_gemm_bf16_kernel(
-    ProjRows<__bf16> ar, DenseRows<__bf16> br, int64_t M, int64_t N, int K, uint16_t* C,
-    int64_t proj_blocks, DenseRows<__bf16> er, DenseRows<__bf16> wr, int64_t M2, int64_t N2, int K2,
-    float* C2) {
-  __shared__ __attribute__((aligned(1024))) char smem[kStages * kStageBytes];
-  if ((int64_t)blockIdx.x < proj_blocks) {
-    const int64_t nt = (N + kBN - 1) / kBN;
-    const int64_t t = xcd_tile(blockIdx.x, (M + kBM - 1) / kBM, nt);
-    if (t < 0) return;
-    gemm_bf16_256<kProjWaves, uint16_t>(ar, br, M, N, K, C, N, (t / nt) * kBM, (t % nt) * kBN, smem);
+// One tile of 256 x 256 at (m0, n0), or part `part` of `sub` of it.
+template <typename OutT, int EPI, class ARows, class BRows>
+__device__ __forceinline__ void gemm_bf16_part(const ARows& ar, const BRows& br, int64_t M, int64_t N,
+                                               int K, OutT* C, int64_t ldc, int64_t m0, int64_t n0,
+                                               bool whole, int sub, int part, char* smem,
+                                               const float* bias) {
+  if (whole) {
+    gemm_bf16<TileWhole, OutT, ARows, BRows, EPI>(ar, br, M, N, K, C, ldc, m0, n0, smem, bias);
+  } else if (sub == 2) {
+    n0 += 128 * part;
+    if (n0 >= N) return;
+    gemm_bf16<TileHalf, OutT, ARows, BRows, EPI>(ar, br, M, N, K, C, ldc, m0, n0, smem, bias);
   } else {
-    const int64_t nt = (N2 + kBN - 1) / kBN;
-    const int64_t t = (int64_t)blockIdx.x - proj_blocks;
-    gemm_bf16_256<kProjWaves, float>(er, wr, M2, N2, K2, C2, N2, (t / nt) * kBM, (t % nt) * kBN,
-                                     smem);
+    m0 += 128 * (part >> 1);
+    n0 += 128 * (part & 1);
+    if (m0 >= M || n0 >= N) return;
+    gemm_bf16<TileQuarter, OutT, ARows, BRows, EPI>(ar, br, M, N, K, C, ldc, m0, n0, smem, bias);
   }
 }
 
-// A bfloat16 product C = A B^T (bfloat16 out) on the 256 x 256 core, tiles in
-// XCD-grouped order, with an optional bias (+ GELU) epilogue.
+// The projection's tiles in banded order (bfloat16 output), then the text
+// projection's (float32 output), cut together: the text tiles are dispatched
+// last, onto compute units that the projection's last round leaves idle.
+template <class Rows>
+struct ProjectArgs {
+  ProjRows<__bf16> ar;
+  Rows br;
+  int64_t M, N;
+  int K;
+  uint16_t* C;
+  Rows er, wr;
+  int64_t M2, N2;
+  int K2;
+  float* C2;
+  int64_t full;
+  int sub;
+};
+
+__device__ __forceinline__ int64_t tiles256(int64_t x) { return (x + 255) / 256; }
+
+__global__ __launch_bounds__(kBfThreads) void project_gemm_bf16_kernel(
+    ProjectArgs<DenseRows<__bf16>> p) {
+  __shared__ __attribute__((aligned(1024))) char smem[TileWhole::LDS];
+  const int64_t mt = tiles256(p.M), nt = tiles256(p.N), nt2 = tiles256(p.N2);
+  int64_t t, m0, n0;
+  int part;
+  bool whole;
+  if (!cut_place(blockIdx.x, mt * nt + tiles256(p.M2) * nt2, p.full, p.sub, t, part, whole)) return;
+  if (t < mt * nt) {
+    banded_tile(t, mt, nt, m0, n0);
+    gemm_bf16_part<uint16_t, kEpiNone>(p.ar, p.br, p.M, p.N, p.K, p.C, p.N, m0, n0, whole, p.sub, part,
+                                       smem, nullptr);
+  } else {
+    t -= mt * nt;
+    gemm_bf16_part<float, kEpiNone>(p.er, p.wr, p.M2, p.N2, p.K2, p.C2, p.N2, (t / nt2) * 256,
+                                    (t % nt2) * 256, whole, p.sub, part, smem, nullptr);
+  }
+}
+
+// The same products in 64 x 64 tiles (cut 16).
+template <class Rows>
+__global__ __launch_bounds__(TileSmall::THREADS) void project_gemm_bf16_small_kernel(ProjectArgs<Rows> p) {
+  __shared__ __attribute__((aligned(1024))) char smem[TileSmall::LDS];
+  const int64_t mt = tiles256(p.M), nt = tiles256(p.N), nt2 = tiles256(p.N2);
+  int64_t t, m0, n0;
+  int part;
+  bool whole;
+  if (!cut_place(blockIdx.x, mt * nt + tiles256(p.M2) * nt2, 0, 16, t, part, whole)) return;
+  const int64_t dm = 64 * (part >> 2), dn = 64 * (part & 3);
+  if (t < mt * nt) {
+    banded_tile(t, mt, nt, m0, n0);
+    if (m0 + dm >= p.M || n0 + dn >= p.N) return;
+    gemm_bf16<TileSmall, uint16_t>(p.ar, p.br, p.M, p.N, p.K, p.C, p.N, m0 + dm, n0 + dn, smem);
+  } else {
+    t -= mt * nt;
+    m0 = (t / nt2) * 256 + dm;
+    n0 = (t % nt2) * 256 + dn;
+    if (m0 >= p.M2 || n0 >= p.N2) return;
+    gemm_bf16<TileSmall, float>(p.er, p.wr, p.M2, p.N2, p.K2, p.C2, p.N2, m0, n0, smem);
+  }
+}
+
+// A bfloat16 product C = A B^T (bfloat16 out), cut as cut_tiles says, with an
+// optional bias (+ GELU) epilogue.
 template <int EPI>
-__global__ __launch_bounds__(64 * kProjWaves) void dense_bf16_kernel(DenseRows<__bf16> ar,
-                                                                    DenseRows<__bf16> br,
-                                                                    int64_t M, int64_t N, int K,
-                                                                    uint16_t* C, const float* bias) {
-  __shared__ __attribute__((aligned(1024))) char smem[kStages * kStageBytes];
-  const int64_t nt = (N + kBN - 1) / kBN;
-  const int64_t t = xcd_tile(blockIdx.x, (M + kBM - 1) / kBM, nt);
-  if (t < 0) return;
-  gemm_bf16_256<kProjWaves, uint16_t, DenseRows<__bf16>, DenseRows<__bf16>, EPI>(
-      ar, br, M, N, K, C, N, (t / nt) * kBM, (t % nt) * kBN, smem, bias);
+__global__ __launch_bounds__(kBfThreads) void dense_bf16_kernel(DenseRows<__bf16> ar,
+                                                                DenseRows<__bf16> br, int64_t M,
+                                                                int64_t N, int K, uint16_t* C,
+                                                                const float* bias, int64_t full,
+                                                                int sub) {
+  __shared__ __attribute__((aligned(1024))) char smem[TileWhole::LDS];
+  const int64_t mt = tiles256(M), nt = tiles256(N);
+  int64_t t, m0, n0;
+  int part;
+  bool whole;
+  if (!cut_place(blockIdx.x, mt * nt, full, sub, t, part, whole)) return;
+  banded_tile(t, mt, nt, m0, n0);
+  gemm_bf16_part<uint16_t, EPI>(ar, br, M, N, K, C, N, m0, n0, whole, sub, part, smem, bias);
+}
+
+// The same in 64 x 64 tiles (cut 16).
+template <int EPI, class Rows>
+__global__ __launch_bounds__(TileSmall::THREADS) void dense_bf16_small_kernel(
+    Rows ar, Rows br, int64_t M, int64_t N, int K, uint16_t* C, const float* bias) {
+  __shared__ __attribute__((aligned(1024))) char smem[TileSmall::LDS];
+  const int64_t mt = tiles256(M), nt = tiles256(N);
+  int64_t t, m0, n0;
+  int part;
+  bool whole;
+  if (!cut_place(blockIdx.x, mt * nt, 0, 16, t, part, whole)) return;
+  banded_tile(t, mt, nt, m0, n0);
+  m0 += 64 * (part >> 2);
+  n0 += 64 * (part & 3);
+  if (m0 >= M || n0 >= N) return;
+  gemm_bf16<TileSmall, uint16_t, Rows, Rows, EPI>(ar, br, M, N, K, C, N, m0, n0, smem, bias);
 }
 
 // grid.x: output tiles, grid.y: K split p, which covers k in [p K, (p + 1) K)
@@ -734,36 +931,34 @@ __global__ __launch_bounds__(256) void gram_edge_kernel(GramArgs a) {
 // token blocks only, [Q] x [K] into A's rows 0..n-1 and [V] x [K] into B's
 // rows 0..n-1 (tq x tq tiles each), and gram_edge_kernel computes the rows
 // and columns of START, STOP and the context split.
-constexpr int kGramWaves = 8;
-
-__global__ __launch_bounds__(64 * kGramWaves) void gram_gemm_bf16_kernel(GramArgs a, int per_group,
-                                                                 int xcd_grouped, int edge) {
-  __shared__ __attribute__((aligned(1024))) char smem[kStages * kStageBytes];
+__global__ __launch_bounds__(kBfThreads) void gram_gemm_bf16_kernel(GramArgs a, int per_group,
+                                                                    int xcd_grouped, int edge) {
+  __shared__ __attribute__((aligned(1024))) char smem[TileWhole::LDS];
   int64_t g, t, g0, n;
   int b;
   if (!gram_tile(blockIdx.x, per_group, a.G, xcd_grouped, g, t)) return;
   if (!gram_group_ok(a, g, t, g0, n, b)) return;
   const __bf16* KQV = static_cast<const __bf16*>(a.KQV);
   if (edge) {
-    const int64_t tq = (a.max_group + kBN - 1) / kBN;
+    const int64_t tq = (a.max_group + 256 - 1) / 256;
     const int64_t sub = t / (tq * tq), tt = t % (tq * tq);
-    const int64_t m0 = (tt / tq) * kBM, n0 = (tt % tq) * kBN;
+    const int64_t m0 = (tt / tq) * 256, n0 = (tt % tq) * 256;
     if (m0 >= n || n0 >= n) return;   // tile outside this (smaller) group
     const int64_t ld3 = 3 * (int64_t)a.h;
     DenseRows<__bf16> ar{KQV + g0 * ld3 + (sub == 0 ? a.h : 2 * a.h), ld3};   // Q or V rows
     DenseRows<__bf16> br{KQV + g0 * ld3, ld3};                               // K rows
     float* C = a.gram + g * a.gram_group_stride + (sub == 0 ? 0 : (n + 1) * a.gram_ld);
-    gemm_bf16_256<kGramWaves, float>(ar, br, n, n, a.h, C, a.gram_ld, m0, n0, smem);
+    gemm_bf16<TileWhole, float>(ar, br, n, n, a.h, C, a.gram_ld, m0, n0, smem);
     return;
   }
   const __bf16* cs = static_cast<const __bf16*>(a.csplit) + (int64_t)b * kGramExtraRows * a.h;
   const int64_t M = 2 * (n + 1) + kGramExtraRows, N = n + 2;
-  const int64_t nt = (a.max_group + 2 + kBN - 1) / kBN;
-  const int64_t m0 = (t / nt) * kBM, n0 = (t % nt) * kBN;
+  const int64_t nt = (a.max_group + 2 + 256 - 1) / 256;
+  const int64_t m0 = (t / nt) * 256, n0 = (t % nt) * 256;
   if (m0 >= M || n0 >= N) return;   // tile outside this (smaller) group
-  GramARows<__bf16> ar{KQV, g0, n, a.T_vis, a.h, cs};
-  GramBRows<__bf16> br{KQV, g0, n, a.T_vis, a.h};
-  gemm_bf16_256<kGramWaves, float>(ar, br, M, N, a.h, a.gram + g * a.gram_group_stride, a.gram_ld, m0, n0,
+  GramARows<__bf16> ar{{}, KQV, g0, n, a.T_vis, a.h, cs};
+  GramBRows<__bf16> br{{}, KQV, g0, n, a.T_vis, a.h};
+  gemm_bf16<TileWhole, float>(ar, br, M, N, a.h, a.gram + g * a.gram_group_stride, a.gram_ld, m0, n0,
                        smem);
 }
 
@@ -783,8 +978,8 @@ __global__ __launch_bounds__(kThreads) void gram_gemm_f32_kernel(GramArgs a, int
   const int64_t nt = (a.max_group + 2 + BN - 1) / BN;
   const int64_t m0 = (t / nt) * BM, n0 = (t % nt) * BN;
   if (m0 >= M || n0 >= N) return;
-  GramARows<float> ar{KQV, g0, n, a.T_vis, a.h, cs};
-  GramBRows<float> br{KQV, g0, n, a.T_vis, a.h};
+  GramARows<float> ar{{}, KQV, g0, n, a.T_vis, a.h, cs};
+  GramBRows<float> br{{}, KQV, g0, n, a.T_vis, a.h};
   gemm_block<float, float, BM, BN, BK>(ar, br, M, N, a.h, a.gram + g * a.gram_group_stride,
                                        a.gram_ld, m0, n0, smem);
 }
@@ -832,18 +1027,28 @@ hipError_t launch_project_gemm(int dtype, const void* X, int64_t T_vis, const vo
                                float* tproj, hipStream_t stream) {
   const int64_t M = T_vis + 2, N = n_out;
   if (dtype == SP_BF16) {
-    ProjRows<__bf16> ar{(const __bf16*)X, T_vis, (const __bf16*)s_start, (const __bf16*)s_stop, d};
-    DenseRows<__bf16> br{(const __bf16*)W, d};
-    DenseRows<__bf16> er{(const __bf16*)E, d_text};
-    DenseRows<__bf16> wr{(const __bf16*)W_text, d_text};
-    const int64_t proj_blocks = ceil_div(ceil_div(M, kBM) * ceil_div(N, kBN), 8) * 8;
-    const int64_t text_blocks = T_txt > 0 ? ceil_div(T_txt, kBM) * ceil_div(h, kBN) : 0;
-    hipLaunchKernelGGL(project_gemm_bf16_kernel, dim3((unsigned)(proj_blocks + text_blocks)),
-                       dim3(64 * kProjWaves), 0, stream, ar, br, M, N, d, (uint16_t*)out,
-                       proj_blocks, er, wr, T_txt, (int64_t)h, d_text, tproj);
+    ProjRows<__bf16> ar{{}, (const __bf16*)X, T_vis, (const __bf16*)s_start, (const __bf16*)s_stop, d};
+    const int64_t T = ceil_div(M, 256) * ceil_div(N, 256) +
+                      ceil_div(T_txt, 256) * ceil_div((int64_t)h, 256);
+    const Cut c = cut_tiles(T);
+    auto args = [&](auto rows) {
+      using R = decltype(rows);
+      auto at = [](const void* p, int64_t ld) { R r; r.base = (const __bf16*)p; r.ld = ld; return r; };
+      return ProjectArgs<R>{ar, at(W, d), M, N, d, (uint16_t*)out, at(E, d_text), at(W_text, d_text),
+                            T_txt, (int64_t)h, d_text, tproj, c.full, c.sub};
+    };
+    if (d > kMaxDenseLd || d_text > kMaxDenseLd)
+      hipLaunchKernelGGL(project_gemm_bf16_small_kernel<WideRows>, dim3((unsigned)small_blocks(T)),
+                         dim3(TileSmall::THREADS), 0, stream, args(WideRows{}));
+    else if (c.sub == 16)
+      hipLaunchKernelGGL(project_gemm_bf16_small_kernel<DenseRows<__bf16>>, dim3((unsigned)c.blocks),
+                         dim3(TileSmall::THREADS), 0, stream, args(DenseRows<__bf16>{}));
+    else
+      hipLaunchKernelGGL(project_gemm_bf16_kernel, dim3((unsigned)c.blocks), dim3(kBfThreads), 0,
+                         stream, args(DenseRows<__bf16>{}));
     return hipGetLastError();
   }
-  ProjRows<float> ar{(const float*)X, T_vis, (const float*)s_start, (const float*)s_stop, d};
+  ProjRows<float> ar{{}, (const float*)X, T_vis, (const float*)s_start, (const float*)s_stop, d};
   DenseRows<float> br{(const float*)W, d};
   if (small_f32_tiles(M, N))
     hipLaunchKernelGGL((project_gemm_kernel<float, float, 64, 64, 32>),
@@ -870,13 +1075,13 @@ hipError_t launch_gram_gemm(const GramArgs& a, hipStream_t stream) {
     // the START / STOP / context entries come from gram_edge_kernel.  (It
     // re-reads the group's rows: at 256-token groups it takes about 300 us
     // on the 64 x 3328 batch against 450 us for the two tiles a group.)
-    const int64_t tq = ceil_div((int64_t)a.max_group, kBN);
-    const int64_t full = ceil_div(M, kBM) * ceil_div(N, kBN);
+    const int64_t tq = ceil_div((int64_t)a.max_group, 256);
+    const int64_t full = ceil_div(M, 256) * ceil_div(N, 256);
     const int edge = a.max_group > 0 && 2 * tq * tq < full;
     const int per_group = (int)(edge ? 2 * tq * tq : full);
     const int64_t blocks =
         xcd_grouped ? 8 * ceil_div(a.G, 8) * per_group : (int64_t)a.G * per_group;
-    hipLaunchKernelGGL(gram_gemm_bf16_kernel, dim3((unsigned)blocks), dim3(64 * kGramWaves), 0, stream, a,
+    hipLaunchKernelGGL(gram_gemm_bf16_kernel, dim3((unsigned)blocks), dim3(kBfThreads), 0, stream, a,
                        per_group, xcd_grouped, edge);
     if (edge)
       hipLaunchKernelGGL(gram_edge_kernel,
@@ -903,18 +1108,34 @@ hipError_t launch_gram_gemm(const GramArgs& a, hipStream_t stream) {
 hipError_t launch_dense_bf16(const void* A, const void* B, int64_t M, int64_t N, int K, void* C,
                              hipStream_t stream, const float* bias, bool gelu) {
   if (M == 0 || N == 0) return hipSuccess;
+  uint16_t* out = (uint16_t*)C;
+  const int64_t T = ceil_div(M, 256) * ceil_div(N, 256);
+  if (K > kMaxDenseLd) {   // only the encoder's text product (no bias) is this wide
+    if (bias) return hipErrorInvalidValue;
+    WideRows wa, wb;
+    wa.base = (const __bf16*)A;
+    wb.base = (const __bf16*)B;
+    wa.ld = wb.ld = K;
+    hipLaunchKernelGGL((dense_bf16_small_kernel<kEpiNone, WideRows>), dim3((unsigned)small_blocks(T)),
+                       dim3(TileSmall::THREADS), 0, stream, wa, wb, M, N, K, out, bias);
+    return hipGetLastError();
+  }
   DenseRows<__bf16> ar{(const __bf16*)A, K};
   DenseRows<__bf16> br{(const __bf16*)B, K};
-  const dim3 grid((unsigned)(ceil_div(ceil_div(M, kBM) * ceil_div(N, kBN), 8) * 8));
-  const dim3 block(64 * kProjWaves);
-  uint16_t* out = (uint16_t*)C;
-  if (!bias)
-    hipLaunchKernelGGL(dense_bf16_kernel<kEpiNone>, grid, block, 0, stream, ar, br, M, N, K, out, bias);
-  else if (!gelu)
-    hipLaunchKernelGGL(dense_bf16_kernel<kEpiBias>, grid, block, 0, stream, ar, br, M, N, K, out, bias);
-  else
-    hipLaunchKernelGGL(dense_bf16_kernel<kEpiBiasGelu>, grid, block, 0, stream, ar, br, M, N, K, out,
-                       bias);
+  const Cut c = cut_tiles(T);
+  const dim3 grid((unsigned)c.blocks);
+  auto launch = [&](auto epi_c) {
+    constexpr int EPI = decltype(epi_c)::value;
+    if (c.sub == 16)
+      hipLaunchKernelGGL((dense_bf16_small_kernel<EPI, DenseRows<__bf16>>), grid, dim3(TileSmall::THREADS), 0, stream, ar, br,
+                         M, N, K, out, bias);
+    else
+      hipLaunchKernelGGL(dense_bf16_kernel<EPI>, grid, dim3(kBfThreads), 0, stream, ar, br, M, N, K, out,
+                         bias, c.full, c.sub);
+  };
+  if (!bias) launch(std::integral_constant<int, kEpiNone>{});
+  else if (!gelu) launch(std::integral_constant<int, kEpiBias>{});
+  else launch(std::integral_constant<int, kEpiBiasGelu>{});
   return hipGetLastError();
 }
 

@@ -26,11 +26,23 @@ __device__ __forceinline__ void lds_dma16(const void* src, char* dst) {
                :: "v"(src), "s"(l) : "memory", "m0");
 }
 
+// The same from a uniform address plus a 32-bit byte offset a lane.
+__device__ __forceinline__ void lds_dma16(const char* base, uint32_t off, char* dst) {
+  const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lptr_t)dst);
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :: "v"(off), "s"(base), "s"(l) : "memory", "m0");
+}
+
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding).
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
+// s_waitcnt for every outstanding LDS access of the wave.
+__device__ __forceinline__ void wait_lgkm0() {
+  __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));
 }
 
 }  // namespace

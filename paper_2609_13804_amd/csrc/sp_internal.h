@@ -148,7 +148,7 @@ struct CompactArgs {
 hipError_t launch_compact(const CompactArgs& a, hipStream_t stream);
 
 // C = A B^T for bfloat16 A [M, K] and B [N, K] (rows K-contiguous), bfloat16
-// C [M, N]; K a multiple of 32.  With bias [N] (float32) each element is
+// C [M, N]; K a multiple of 64.  With bias [N] (float32) each element is
 // bf16(bf16(product) + bias), or bf16(GELU(bf16(product) + bias)) with gelu:
 // what a separate bias (+ GELU) pass over the stored product gives.
 hipError_t launch_dense_bf16(const void* A, const void* B, int64_t M, int64_t N, int K, void* C,
