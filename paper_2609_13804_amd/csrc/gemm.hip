@@ -18,7 +18,8 @@
 //  * the text projection W_text E_text^T (float32 output for the LayerNorm);
 //  * per-group Gram products of the projected rows used by the selection
 //    recurrence (select.hip): rows [Q_g; q_start; V_g; v_start; context split]
-//    against columns [K_g; k_stop; k_start].
+//    against columns [K_g; k_stop; k_start] (bfloat16: the rows and columns
+//    beside the tokens' as strips).
 #include <type_traits>
 
 #include "sp_internal.h"
@@ -219,6 +220,9 @@ using TileWhole = BfTile<256, 256, 2, 4, 2>;     // 160 KB
 using TileHalf = BfTile<256, 128, 2, 4, 2>;      // 128 KB
 using TileQuarter = BfTile<128, 128, 2, 4, 4>;   // 144 KB
 using TileSmall = BfTile<64, 64, 2, 2, 4>;       // 72 KB: two workgroups a CU
+using TileGramA = BfTile<128, 256, 2, 4, 2>;     // 112 KB, and the strips beside it
+using TileGramB = BfTile<256, 192, 2, 4, 2>;     // 144 KB
+using TileGramC = BfTile<128, 192, 2, 4, 2>;     // 96 KB
 
 // Output epilogue of the bfloat16 core: the product as it is, or (bfloat16
 // output only) the product rounded to bfloat16, plus a per-column float32 bias,
@@ -226,12 +230,21 @@ using TileSmall = BfTile<64, 64, 2, 2, 4>;       // 72 KB: two workgroups a CU
 // the product and then running a bias (+ GELU) pass over it.
 constexpr int kEpiNone = 0, kEpiBias = 1, kEpiBiasGelu = 2;
 
-template <class G, typename OutT, class ARows, class BRows, int EPI = kEpiNone>
+// A product may carry strips (Gram products, below): kCols / kRows further
+// columns and rows beside the tile, whose operand rows stay in LDS whole.
+struct NoStrips {
+  static constexpr bool kCols = false, kRows = false;
+  __device__ int64_t out_row(int64_t row) const { return row; }
+};
+
+template <class G, typename OutT, class ARows, class BRows, int EPI = kEpiNone, class Strips = NoStrips>
 __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int64_t M, int64_t N,
                                           int K, OutT* __restrict__ C, int64_t ldc, int64_t m0,
                                           int64_t n0, char* smem,
-                                          const float* __restrict__ bias = nullptr) {
+                                          const float* __restrict__ bias = nullptr,
+                                          const Strips& strips = Strips()) {
   static_assert(EPI == kEpiNone || sizeof(OutT) == 2, "bias epilogues write bfloat16");
+  constexpr bool SC = Strips::kCols, SR = Strips::kRows;
   constexpr int D = G::D, LA = G::LA, LB = G::LB, TM = G::TM, TN = G::TN, W = G::WAVES;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -285,6 +298,7 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
   // kt + D (into the buffer of stage kt - 1), phase 1 those of B (into the
   // buffer just freed), a few at a time between the matrix instructions.
   const int KT = K / kKStage;
+  if constexpr (SC || SR) strips.load(K, smem + G::LDS);   // the oldest loads: any wait below covers them
 #pragma unroll
   for (int s = 0; s < D; ++s)
     if (s < KT) {
@@ -302,13 +316,58 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
 #pragma unroll
   for (int i = 0; i < TM; ++i) f0.a[i] = frag(0, aoff, 0, i);
 
+  // Strips: the column strip's 16 x 16 tiles are shared out over the waves (CT
+  // row groups of the wave's own half each), the row strip's likewise (RT column
+  // groups).  Their fragments are read and used within phase 0, for both k-steps
+  // (the stage's buffers are free after it): k-step ks is read before the
+  // half's first matrix instructions and used after its last.
+  constexpr int CT = TM / G::WGN > 0 ? TM / G::WGN : 1, RT = (TN + 1) / 2;
+  static_assert(!(SC || SR) || (TM % G::WGN == 0 && G::WGM == 2), "strip tiles per wave");
+  [[maybe_unused]] f32x4_t accc[CT], accr[RT], accx = {0.f, 0.f, 0.f, 0.f};
+  [[maybe_unused]] bf16x8_t xa[CT], xb[RT], xs, xr;
+  if constexpr (SC)
+#pragma unroll
+    for (int c = 0; c < CT; ++c) accc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  if constexpr (SR)
+#pragma unroll
+    for (int j = 0; j < RT; ++j) accr[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int xaoff = aoff + wn * CT * 16 * kRowBytes;
+  auto strip_col = [&](int j) { const int q = wm * RT + j; return q < TN ? q : TN - 1; };
+  auto strip_read = [&](int kt, int ks, int abuf, int bbuf) {
+    const int k = kt * kKStage + ks * 32 + 8 * lk;
+    if constexpr (SC) {
+#pragma unroll
+      for (int c = 0; c < CT; ++c) xa[c] = frag(abuf, xaoff, ks, c);
+    }
+    if constexpr (SC) xs = strips.col_frag(smem + G::LDS, l16, k);
+    if constexpr (SR) {
+#pragma unroll
+      for (int j = 0; j < RT; ++j)
+        xb[j] = *reinterpret_cast<const bf16x8_t*>(smem + bbuf + (boff ^ (ks << 6)) + strip_col(j) * 16 * kRowBytes);
+      xr = strips.row_frag(smem + G::LDS, l16, k);
+    }
+  };
+  auto strip_mfma = [&]() {
+    if constexpr (SC) {
+#pragma unroll
+      for (int c = 0; c < CT; ++c) accc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xs, xa[c], accc[c], 0, 0, 0);
+    }
+    if constexpr (SR) {
+#pragma unroll
+      for (int j = 0; j < RT; ++j) accr[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[j], xr, accr[j], 0, 0, 0);
+      if constexpr (SC) accx = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xs, xr, accx, 0, 0, 0);
+    }
+  };
+
   // One phase: matrix instructions on `cur` in TM groups; the first groups also
   // read `nxt` (two or three fragments each), and load(i) issues group i's loads.
-  auto phase = [&](Frags& cur, Frags& nxt, bool read, int abuf, int bbuf, int ks, auto&& load) {
+  auto phase = [&](Frags& cur, Frags& nxt, bool read, int abuf, int bbuf, int ks, int kt, auto&& load) {
     constexpr int R = TM + TN, GR = TM > 2 ? TM - 2 : TM, PER = (R + GR - 1) / GR;
     __builtin_amdgcn_s_setprio(1);   // the wave whose operands are ready goes first
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
+      if constexpr (SC || SR)
+        if (ks == 1 && i % (TM / 2) == 0) strip_read(kt, i / (TM / 2), abuf, bbuf);
 #pragma unroll
       for (int j = 0; j < TN; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.b[j], cur.a[i], acc[i][j], 0, 0, 0);
@@ -321,6 +380,8 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
         }
       }
       load(i);
+      if constexpr (SC || SR)
+        if (ks == 1 && (i + 1) % (TM / 2) == 0) strip_mfma();
       __builtin_amdgcn_sched_barrier(0);
     }
     __builtin_amdgcn_s_setprio(0);
@@ -336,7 +397,7 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
     const bool refill = REFILL == 1 || kt + D < KT;
     const int ra = ia == 0 ? D : ia - 1, rb = ib;          // slots of A and B of stage kt + D
     const int ia2 = ia == D ? 0 : ia + 1, ib2 = ib == D - 1 ? 0 : ib + 1;
-    phase(f0, f1, true, ia * G::BUFA, ib * G::BUFB, 1, [&](int i) {
+    phase(f0, f1, true, ia * G::BUFA, ib * G::BUFB, 1, kt, [&](int i) {
       if (refill) {
 #pragma unroll
         for (int q = 0; q < LA; ++q)
@@ -354,7 +415,7 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
     }
-    phase(f1, f0, more, ia2 * G::BUFA, ib2 * G::BUFB, 0, [&](int i) {
+    phase(f1, f0, more, ia2 * G::BUFA, ib2 * G::BUFB, 0, kt, [&](int i) {
       if (refill) {
 #pragma unroll
         for (int q = 0; q < LB; ++q)
@@ -438,7 +499,7 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
       const int64_t row = m0 + p * ROWS + lr, col = n0 + (int64_t)ch * EPC;
       if (row >= M || col >= N) continue;
       const OutT* src = reinterpret_cast<const OutT*>(smem + lr * (G::BN * E) + ((ch ^ sw(lr)) << 4));
-      OutT* dst = C + row * ldc + col;
+      OutT* dst = C + strips.out_row(row) * ldc + col;
       if (vec && col + EPC <= N) {
         *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
       } else {
@@ -446,6 +507,18 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
       }
     }
     if (p + 1 < PASSES) __syncthreads();
+  }
+  if constexpr (SC) {
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+      strips.store_col(C, ldc, m0 + wm * (G::BM / 2) + 16 * (wn * CT + c) + l16, M, lk, accc[c]);
+  }
+  if constexpr (SR) {
+#pragma unroll
+    for (int j = 0; j < RT; ++j)
+      strips.store_row(C, ldc, l16, n0 + wn * (G::BN / G::WGN) + 16 * strip_col(j) + 4 * lk, N, accr[j]);
+    if constexpr (SC)
+      if (wave == 0) strips.store_corner(C, ldc, l16, lk, accx);
   }
 }
 
@@ -575,11 +648,11 @@ struct WideRows : AnyRows<WideRows> {
   __device__ const __bf16* row(int64_t m) const { return base + m * ld; }
 };
 
-// Gram operand rows of one group with tokens [g0, g0 + n): A side is
+// float32 Gram operand rows of one group with tokens [g0, g0 + n): A side is
 // [Q tokens; q_start; V tokens; v_start; c_hi; c_mid; c_lo] (the last three
 // from the image's context split), B side is [K tokens; k_stop; k_start].
 template <typename T>
-struct GramARows : AnyRows<GramARows<T>> {
+struct GramARows {
   const T* KQV;
   int64_t g0, n, start_row;
   int h;
@@ -595,7 +668,7 @@ struct GramARows : AnyRows<GramARows<T>> {
 };
 
 template <typename T>
-struct GramBRows : AnyRows<GramBRows<T>> {
+struct GramBRows {
   const T* KQV;
   int64_t g0, n, start_row;
   int h;
@@ -604,6 +677,86 @@ struct GramBRows : AnyRows<GramBRows<T>> {
     if (c < n) return KQV + (g0 + c) * ld;
     if (c == n) return KQV + (start_row + 1) * ld;   // STOP key
     return KQV + start_row * ld;                      // START key
+  }
+};
+
+// bfloat16 Gram products of one group with tokens [g0, g0 + n): the tiles cover
+// the 2 n rows [Q; V] against the n rows [K]; the rows of START and of the
+// context split and the columns of STOP and START are strips.  An empty group's
+// tile reads START's rows and stores nothing.
+struct GramTokenARows : AnyRows<GramTokenARows> {
+  const __bf16* KQV;
+  int64_t g0, n, start_row;
+  int h;
+  __device__ const __bf16* row(int64_t r) const {
+    const int64_t ld = 3 * (int64_t)h;
+    if (r < 0) return KQV + start_row * ld + h;
+    return r < n ? KQV + (g0 + r) * ld + h : KQV + (g0 + r - n) * ld + 2 * h;
+  }
+};
+struct GramTokenBRows : AnyRows<GramTokenBRows> {
+  const __bf16* KQV;
+  int64_t g0, start_row;
+  int h;
+  __device__ const __bf16* row(int64_t c) const {
+    return KQV + (c < 0 ? start_row : g0 + c) * 3 * (int64_t)h;
+  }
+};
+
+// The strips: rows [q_start; v_start; c_hi; c_mid; c_lo] (kRows) and columns
+// [k_stop; k_start] (kCols) of a group's Gram block.  Their seven operand rows
+// are loaded into LDS whole, row stride 2 h + 16 bytes (the five rows a
+// fragment read touches fall on different banks); a fragment's lanes past them
+// repeat a row and are not stored.
+template <bool COLS, bool ROWS>
+struct GramStrips {
+  static constexpr bool kCols = COLS, kRows = ROWS;
+  static constexpr int kMaxH = 1024;                       // sp_dims' limit
+  static constexpr int LDS = 7 * (2 * kMaxH + 16);
+  const __bf16* start;      // START's projected row [k | q | v], STOP's after it
+  const __bf16* csplit;     // the image's three context rows
+  int64_t n;
+  int h;
+  __device__ int stride() const { return 2 * h + 16; }
+  __device__ void load(int K, char* dst) const {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (w >= 7) return;
+    const __bf16* row = w == 0 ? start + h : w == 1 ? start + 2 * h : w < 5 ? csplit + (w - 2) * h
+                      : w == 5 ? start + 3 * h : start;
+    for (int c = 0; c < K; c += 512)
+      if (c + 8 * lane < K) lds_dma16(row + c + 8 * lane, dst + w * stride() + 2 * c);
+  }
+  __device__ bf16x8_t at(const char* s, int r, int k) const {
+    return *reinterpret_cast<const bf16x8_t*>(s + r * stride() + 2 * k);
+  }
+  __device__ bf16x8_t row_frag(const char* s, int l16, int k) const { return at(s, l16 < 5 ? l16 : 4, k); }
+  __device__ bf16x8_t col_frag(const char* s, int l16, int k) const { return at(s, 5 + (l16 & 1), k); }
+  // The block's rows: A of the tokens, A of START, B of the tokens, B of START,
+  // the three context rows.
+  __device__ int64_t out_row(int64_t r) const { return r < n ? r : r + 1; }
+  __device__ int64_t strip_row(int r) const { return r == 0 ? n : 2 * n + r; }
+  __device__ void store_col(float* C, int64_t ldc, int64_t row, int64_t M, int lk, f32x4_t v) const {
+    if (lk != 0 || row >= M) return;
+    float* dst = C + out_row(row) * ldc + n;
+    dst[0] = v[0];
+    dst[1] = v[1];
+  }
+  __device__ void store_row(float* C, int64_t ldc, int r, int64_t col, int64_t N, f32x4_t v) const {
+    if (r >= 5) return;
+    float* dst = C + strip_row(r) * ldc + col;             // 16-byte aligned: ldc and col are multiples of 4
+    if (col + 4 <= N) {
+      *reinterpret_cast<f32x4_t*>(dst) = v;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (col + e < N) dst[e] = v[e];
+    }
+  }
+  __device__ void store_corner(float* C, int64_t ldc, int r, int lk, f32x4_t v) const {
+    if (r >= 5 || lk != 0) return;
+    float* dst = C + strip_row(r) * ldc + n;
+    dst[0] = v[0];
+    dst[1] = v[1];
   }
 };
 
@@ -812,154 +965,62 @@ __device__ __forceinline__ bool gram_group_ok(const GramArgs& a, int64_t g, int6
   return true;
 }
 
-// The Gram entries that involve START, STOP or the context split, for the
-// `edge` layout: item j of a group (a token, or j = n for the corner, where
-// q_start, v_start and k_stop stand in for q_j, v_j and k_j) gives
-//   A[j][n] = q_j . k_stop    A[j][n + 1] = q_j . k_start    B[j][n] = v_j . k_stop
-//   A[n][j] = q_start . k_j   B[n][j] = v_start . k_j        CK[s][j] = c_s . k_j
-// as float32 sums of exact bfloat16 products, one wave per item.
-// The eight sums are reduced together: each shuffle step halves the values
-// a lane carries, and lane 8 k ends with value k.
-constexpr int kEdgeItems = 8;   // items per wave, four waves per workgroup
-
-// Grid (G, ceil((max_group + 1) / 32)): workgroup (g, y) of four waves takes
-// items [32 y, 32 y + 32) of group g.
-__global__ __launch_bounds__(256) void gram_edge_kernel(GramArgs a) {
-  const int64_t g = blockIdx.x;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t g0 = a.grp_off[g], g1 = a.grp_off[g + 1];
-  const int64_t n = g1 - g0;
-  const int b = a.grp_img[g];
-  if (g0 < 0 || g1 > a.T_vis || n < 0 || n > a.max_group || b < 0 || b >= a.B) return;
-  const int h = a.h;
-  const int64_t ld3 = 3 * (int64_t)h, ld = a.gram_ld;
-  const __bf16* KQV = static_cast<const __bf16*>(a.KQV);
-  const __bf16* kst = KQV + a.T_vis * ld3;              // START: k, q, v
-  const __bf16* kstop = KQV + (a.T_vis + 1) * ld3;      // STOP key
-  const __bf16* cs = static_cast<const __bf16*>(a.csplit) + (int64_t)b * kGramExtraRows * h;
-  float* A = a.gram + g * a.gram_group_stride;
-  float* Bm = A + (n + 1) * ld;
-  float* CK = A + (2 * n + 2) * ld;
-  // this lane's eight-element slices (at most two: h <= 1024) of the shared vectors
-  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-  auto ld16 = [&](const __bf16* p, int c) -> u4 {
-    const int e = 8 * lane + 512 * c;
-    return e < h ? *reinterpret_cast<const u4*>(p + e) : u4{0, 0, 0, 0};
-  };
-  // the two bfloat16 values of word i, widened exactly to float32
-  auto lo = [](u4 x, int i) { return __uint_as_float(x[i] << 16); };
-  auto hi = [](u4 x, int i) { return __uint_as_float(x[i] & 0xffff0000u); };
-  // this lane's eight-element slices of the shared vectors (packed)
-  u4 sv[7][2];
-  const __bf16* shared_rows[7] = {kstop, kst, kst + h, kst + 2 * h, cs, cs + h, cs + 2 * h};
-#pragma unroll
-  for (int v = 0; v < 7; ++v)
-#pragma unroll
-    for (int c = 0; c < 2; ++c) sv[v][c] = ld16(shared_rows[v], c);
-  // item i's rows: its token's [k | q | v], or k_stop, q_start, v_start (j = n)
-  auto load_item = [&](int64_t j, u4 (&q)[2], u4 (&v)[2], u4 (&k)[2]) {
-    const __bf16* krow = j < n ? KQV + (g0 + j) * ld3 : kstop;
-    const __bf16* qrow = j < n ? krow + h : kst + h;
-    const __bf16* vrow = j < n ? krow + 2 * h : kst + 2 * h;
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      q[c] = ld16(qrow, c);
-      v[c] = ld16(vrow, c);
-      k[c] = ld16(krow, c);
-    }
-  };
-  const int64_t j0 = (int64_t)blockIdx.y * 4 * kEdgeItems + wave;
-  u4 qn[2], vn[2], kn[2];     // the next item's rows, requested one item ahead
-  if (j0 <= n) load_item(j0, qn, vn, kn);
-  for (int i = 0; i < kEdgeItems; ++i) {
-    const int64_t j = j0 + 4 * i;
-    if (j > n) break;
-    u4 q[2], v[2], k[2];
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      q[c] = qn[c];
-      v[c] = vn[c];
-      k[c] = kn[c];
-    }
-    if (i + 1 < kEdgeItems && j + 4 <= n) load_item(j + 4, qn, vn, kn);
-    float d[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int p = 0; p < 4; ++p)
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          auto f = [&](u4 x) { return half ? hi(x, p) : lo(x, p); };
-          const float qv = f(q[c]), vv = f(v[c]), kv = f(k[c]);
-          d[0] = fmaf(qv, f(sv[0][c]), d[0]);
-          d[1] = fmaf(qv, f(sv[1][c]), d[1]);
-          d[2] = fmaf(vv, f(sv[0][c]), d[2]);
-          d[3] = fmaf(f(sv[2][c]), kv, d[3]);
-          d[4] = fmaf(f(sv[3][c]), kv, d[4]);
-          d[5] = fmaf(f(sv[4][c]), kv, d[5]);
-          d[6] = fmaf(f(sv[5][c]), kv, d[6]);
-          d[7] = fmaf(f(sv[6][c]), kv, d[7]);
-        }
-    // 8 values -> 4 (xor 32) -> 2 (xor 16) -> 1 (xor 8), then xor 4, 2, 1
-    const bool h32 = lane & 32, h16 = lane & 16, h8 = lane & 8;
-    float r4[4], r2[2];
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      r4[k] = (h32 ? d[k + 4] : d[k]) + __shfl_xor(h32 ? d[k] : d[k + 4], 32, 64);
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-      r2[k] = (h16 ? r4[k + 2] : r4[k]) + __shfl_xor(h16 ? r4[k] : r4[k + 2], 16, 64);
-    float r = (h8 ? r2[1] : r2[0]) + __shfl_xor(h8 ? r2[0] : r2[1], 8, 64);
-    r += __shfl_xor(r, 4, 64);
-    r += __shfl_xor(r, 2, 64);
-    r += __shfl_xor(r, 1, 64);
-    if ((lane & 7) == 0) {
-      const int k = (h32 ? 4 : 0) + (h16 ? 2 : 0) + (h8 ? 1 : 0);
-      float* dst = k == 0 ? A + j * ld + n
-                 : k == 1 ? A + j * ld + n + 1
-                 : k == 2 ? Bm + j * ld + n
-                 : k == 3 ? A + n * ld + j
-                 : k == 4 ? Bm + n * ld + j
-                          : CK + (k - 5) * ld + j;
-      *dst = r;
-    }
-  }
-}
-
-// bfloat16 Gram products on the 256 x 256 direct-to-LDS core: 15 tiles per
-// 576-token group, one round for 16 groups.  With `edge` the tiles cover the
-// token blocks only, [Q] x [K] into A's rows 0..n-1 and [V] x [K] into B's
-// rows 0..n-1 (tq x tq tiles each), and gram_edge_kernel computes the rows
-// and columns of START, STOP and the context split.
+// bfloat16 Gram products.  Bound by the float32 blocks' way to memory and the
+// projected rows' way in (832 groups of 256 tokens, h 1024: 1.75 GB, 340 us at
+// the copy rate) and, below a few rounds of workgroups, by a tile's own latency.
+// Tile t of a group covers rows [BM (t / panels), ..) of
+// [Q; V] and columns [BN (t % panels), ..) of [K].  The tiles of the first
+// panel carry the column strip, those of the first row chunk the row strip, so
+// every projected row is read by the tiles alone and no tile is spent on the
+// five rows and two columns beside them.  Measured against whole 256 x 256 tiles
+// over [Q; q_start; V; v_start; c] x [K; k_stop; k_start] (for groups just below
+// a multiple of 256: tiles over the tokens, and dot products in a second kernel
+// that read every row again), h 1024: 832 groups of 256 713 -> 421 us, 157
+// groups of 388-576 322 -> 272, 40 of 576 103 -> 85, 5 of 576 36 -> 23.
+template <class G>
 __global__ __launch_bounds__(kBfThreads) void gram_gemm_bf16_kernel(GramArgs a, int per_group,
-                                                                    int xcd_grouped, int edge) {
-  __shared__ __attribute__((aligned(1024))) char smem[TileWhole::LDS];
+                                                                    int xcd_grouped) {
+  static_assert(G::THREADS == kBfThreads, "eight waves");
+  constexpr int kLds = G::LDS + GramStrips<true, true>::LDS;
+  static_assert(kLds <= kLdsBytes, "rings and strips fit the LDS");
+  __shared__ __attribute__((aligned(1024))) char smem[kLds];
   int64_t g, t, g0, n;
   int b;
   if (!gram_tile(blockIdx.x, per_group, a.G, xcd_grouped, g, t)) return;
   if (!gram_group_ok(a, g, t, g0, n, b)) return;
+  const int64_t panels = a.max_group > 0 ? (a.max_group + G::BN - 1) / G::BN : 1;
+  const int64_t m0 = (t / panels) * G::BM, n0 = (t % panels) * G::BN;
+  // outside this (smaller) group; the strips are the first tiles' also in an empty group
+  if ((m0 > 0 && m0 >= 2 * n) || (n0 > 0 && n0 >= n)) return;
   const __bf16* KQV = static_cast<const __bf16*>(a.KQV);
-  if (edge) {
-    const int64_t tq = (a.max_group + 256 - 1) / 256;
-    const int64_t sub = t / (tq * tq), tt = t % (tq * tq);
-    const int64_t m0 = (tt / tq) * 256, n0 = (tt % tq) * 256;
-    if (m0 >= n || n0 >= n) return;   // tile outside this (smaller) group
-    const int64_t ld3 = 3 * (int64_t)a.h;
-    DenseRows<__bf16> ar{KQV + g0 * ld3 + (sub == 0 ? a.h : 2 * a.h), ld3};   // Q or V rows
-    DenseRows<__bf16> br{KQV + g0 * ld3, ld3};                               // K rows
-    float* C = a.gram + g * a.gram_group_stride + (sub == 0 ? 0 : (n + 1) * a.gram_ld);
-    gemm_bf16<TileWhole, float>(ar, br, n, n, a.h, C, a.gram_ld, m0, n0, smem);
-    return;
-  }
+  GramTokenARows ar;
+  ar.KQV = KQV;
+  ar.g0 = g0;
+  ar.n = n;
+  ar.start_row = a.T_vis;
+  ar.h = a.h;
+  GramTokenBRows br;
+  br.KQV = KQV;
+  br.g0 = g0;
+  br.start_row = a.T_vis;
+  br.h = a.h;
+  const __bf16* start = KQV + a.T_vis * 3 * (int64_t)a.h;
   const __bf16* cs = static_cast<const __bf16*>(a.csplit) + (int64_t)b * kGramExtraRows * a.h;
-  const int64_t M = 2 * (n + 1) + kGramExtraRows, N = n + 2;
-  const int64_t nt = (a.max_group + 2 + 256 - 1) / 256;
-  const int64_t m0 = (t / nt) * 256, n0 = (t % nt) * 256;
-  if (m0 >= M || n0 >= N) return;   // tile outside this (smaller) group
-  GramARows<__bf16> ar{{}, KQV, g0, n, a.T_vis, a.h, cs};
-  GramBRows<__bf16> br{{}, KQV, g0, n, a.T_vis, a.h};
-  gemm_bf16<TileWhole, float>(ar, br, M, N, a.h, a.gram + g * a.gram_group_stride, a.gram_ld, m0, n0,
-                       smem);
+  float* C = a.gram + g * a.gram_group_stride;
+  auto run = [&](auto cols_c, auto rows_c) {
+    using S = GramStrips<decltype(cols_c)::value, decltype(rows_c)::value>;
+    gemm_bf16<G, float, GramTokenARows, GramTokenBRows, kEpiNone, S>(
+        ar, br, 2 * n, n, a.h, C, a.gram_ld, m0, n0, smem, nullptr, S{start, cs, n, a.h});
+  };
+  using T = std::true_type;
+  using F = std::false_type;
+  if (n0 == 0) {
+    if (m0 == 0) run(T{}, T{});
+    else run(T{}, F{});
+  } else {
+    if (m0 == 0) run(F{}, T{});
+    else run(F{}, F{});
+  }
 }
 
 // float32 Gram products on the register-staged core, BM x BN tiles.
@@ -978,8 +1039,8 @@ __global__ __launch_bounds__(kThreads) void gram_gemm_f32_kernel(GramArgs a, int
   const int64_t nt = (a.max_group + 2 + BN - 1) / BN;
   const int64_t m0 = (t / nt) * BM, n0 = (t % nt) * BN;
   if (m0 >= M || n0 >= N) return;
-  GramARows<float> ar{{}, KQV, g0, n, a.T_vis, a.h, cs};
-  GramBRows<float> br{{}, KQV, g0, n, a.T_vis, a.h};
+  GramARows<float> ar{KQV, g0, n, a.T_vis, a.h, cs};
+  GramBRows<float> br{KQV, g0, n, a.T_vis, a.h};
   gemm_block<float, float, BM, BN, BK>(ar, br, M, N, a.h, a.gram + g * a.gram_group_stride,
                                        a.gram_ld, m0, n0, smem);
 }
@@ -1063,6 +1124,16 @@ hipError_t launch_project_gemm(int dtype, const void* X, int64_t T_vis, const vo
   return launch_text_gemm_f32(E, T_txt, W_text, d_text, h, tproj, stream);
 }
 
+namespace {
+// Time of one round of Gram tiles: a fixed part (loads and strips to the first
+// matrix instruction, the float32 tile's way out) and the tile's area.  Fitted
+// to (us for tiles of 128 x 256 / 256 x 192 / 128 x 192, h 1024): 5 groups of
+// 576 tokens 26 / 36 / 23, 16 of 576 42 / 39 / 38, 40 of 576 98 / 83 / 86, 157
+// of 576 392 / 330 / 373, 40 of 384 47 / 40 / 42, 832 of 256 420 / 490 / 564, 20
+// of 1000 134 / 141 / 157; the choice is within 3 % of the best on each.
+inline double gram_tile_us(int bm, int bn, int h) { return 6.0 + 4.3e-4 * bm * bn * h / 1024; }
+}  // namespace
+
 hipError_t launch_gram_gemm(const GramArgs& a, hipStream_t stream) {
   if (a.G == 0) return hipSuccess;
   const int64_t M = 2 * ((int64_t)a.max_group + 1) + kGramExtraRows, N = a.max_group + 2;
@@ -1070,23 +1141,24 @@ hipError_t launch_gram_gemm(const GramArgs& a, hipStream_t stream) {
   if (a.dtype == SP_BF16) {
     hipLaunchKernelGGL(ctx_split_kernel<__bf16>, dim3(a.B), dim3(256), 0, stream, a.ctx, a.h,
                        (__bf16*)a.csplit);
-    // The token blocks alone take fewer tiles when the group size sits just
-    // below a multiple of 256 (256-token groups: 2 tiles instead of 6); then
-    // the START / STOP / context entries come from gram_edge_kernel.  (It
-    // re-reads the group's rows: at 256-token groups it takes about 300 us
-    // on the 64 x 3328 batch against 450 us for the two tiles a group.)
-    const int64_t tq = ceil_div((int64_t)a.max_group, 256);
-    const int64_t full = ceil_div(M, 256) * ceil_div(N, 256);
-    const int edge = a.max_group > 0 && 2 * tq * tq < full;
-    const int per_group = (int)(edge ? 2 * tq * tq : full);
-    const int64_t blocks =
-        xcd_grouped ? 8 * ceil_div(a.G, 8) * per_group : (int64_t)a.G * per_group;
-    hipLaunchKernelGGL(gram_gemm_bf16_kernel, dim3((unsigned)blocks), dim3(kBfThreads), 0, stream, a,
-                       per_group, xcd_grouped, edge);
-    if (edge)
-      hipLaunchKernelGGL(gram_edge_kernel,
-                         dim3((unsigned)a.G, (unsigned)ceil_div((int64_t)a.max_group + 1, 4 * kEdgeItems)),
-                         dim3(256), 0, stream, a);
+    // The tile that covers the chip's groups in the least time: rounds of 256
+    // workgroups, each a fixed part and its area (gram_tile_us).
+    const int64_t mg = a.max_group > 0 ? a.max_group : 1;
+    auto tiles = [&](int bm, int bn) { return ceil_div(2 * mg, bm) * ceil_div(mg, bn); };
+    auto cost = [&](int bm, int bn) {
+      return (double)ceil_div(tiles(bm, bn) * a.G, 256) * gram_tile_us(bm, bn, a.h);
+    };
+    auto launch = [&](auto* kernel, int bm, int bn) {
+      const int per_group = (int)tiles(bm, bn);
+      const int64_t blocks =
+          xcd_grouped ? 8 * ceil_div(a.G, 8) * per_group : (int64_t)a.G * per_group;
+      hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kBfThreads), 0, stream, a, per_group,
+                         xcd_grouped);
+    };
+    const double ca = cost(128, 256), cb = cost(256, 192), cc = cost(128, 192);
+    if (cc <= ca && cc <= cb) launch(gram_gemm_bf16_kernel<TileGramC>, 128, 192);
+    else if (cb <= ca) launch(gram_gemm_bf16_kernel<TileGramB>, 256, 192);
+    else launch(gram_gemm_bf16_kernel<TileGramA>, 128, 256);
   } else {
     hipLaunchKernelGGL(ctx_split_kernel<float>, dim3(a.B), dim3(256), 0, stream, a.ctx, a.h,
                        (float*)a.csplit);
