@@ -20,6 +20,8 @@
 // row 2n+1 the B row of START, rows 2n+2 .. 2n+4 three parts of cK whose sum
 // is cK (the context enters the products as three rows of the working dtype);
 // columns [0, n) tokens, n STOP, n+1 START.
+#include <type_traits>
+
 #include "sp_internal.h"
 
 namespace sp {
@@ -188,6 +190,496 @@ __device__ __forceinline__ int key_index(uint64_t k) {
   return (int)(0xffffffffu - (uint32_t)k);
 }
 
+// Checks group g's offsets, size, cap and image; otherwise thread 0 records the
+// error and the group keeps nothing.
+__device__ __forceinline__ bool group_valid(const SelParams& p, int g, int per_round, int tid) {
+  const int64_t g0 = p.grp_off[g], g1 = p.grp_off[g + 1];
+  const int64_t n = g1 - g0;
+  const int cap = p.grp_cap[g], b = p.grp_img[g];
+  int code = 0;
+  if (g0 < 0 || g1 < g0 || g1 > p.T_vis || b < 0 || b >= p.B) code = SP_DEV_BAD_OFFSETS;
+  else if (n > p.max_group) code = SP_DEV_GROUP_TOO_LARGE;
+  else if (cap < 0 || (int64_t)p.max_cap < ((int64_t)cap * per_round < n ? (int64_t)cap * per_round : n))
+    code = SP_DEV_BAD_CAP;
+  else if (g0 < p.img_off[b] || g1 > p.img_off[b + 1]) code = SP_DEV_BAD_OFFSETS;
+  if (!code) return true;
+  if (tid == 0) {
+    set_device_error(p.err, code);
+    p.grp_count[g] = 0;
+    if (p.grp_cnt_out) p.grp_cnt_out[g] = 0;
+  }
+  return false;
+}
+
+// ------------------------------------------------------------------ one token a round, registers only
+//
+// The recurrence for g = 1, groups of up to 576 tokens and up to 64 NSEG + 1
+// history entries (caps of 64, 128, 192): the whole history stays in registers.
+// Thread j of the W <= 8 waves owns column j; with SEC, wave w also owns the
+// eight columns 512 + 8 w ...
+//
+// What bounds it: one chain per step (the newest row's load, the softmax over
+// the history, the columns' sums, the decision, one barrier), and what the two
+// waves of a SIMD issue on the way: the general kernel below issues 569
+// instructions a wave and step, 112 of them the sums' FMAs.  So the history is
+// cut into blocks of 16 entries and the step is compiled per block: which
+// registers a step reads, and how many of the history's lanes exist, are then
+// constants, and the bookkeeping (history columns, STOP values) is one select
+// each.  The open block's B values wait in LDS, each thread's in its own row (an
+// indexed register write would copy the register tuple), and move to registers
+// when the block is full.  The 64 softmax weights of a segment (four blocks) are
+// one register, lane i the i-th; two row exchanges (permlane32_swap,
+// permlane16_swap) spread each of its four rows over the wave, and an FMA takes
+// weight i of a row through its DPP operand (row_newbcast), so the sums read no
+// LDS.  The second columns keep their history in LDS by entry: a lane weighs the
+// entries of its own weights for the wave's eight columns, and a folding
+// exchange adds the lanes.
+//
+// us per step over the first 64, the next 64 and the last 64 of 192 steps, 16
+// groups (start: the general kernel): 576 tokens 1.83, 2.07, 2.40 -> 1.17, 1.54,
+// 1.94; 512 tokens 1.74, 2.07, 2.29 -> 0.97, 1.32, 1.69; 256 tokens 1.44, 1.68,
+// 1.90 -> 0.81, 1.02, 1.26; 64 tokens 1.14 -> 0.71.  Kept as one loop body for
+// all blocks (uniform branches instead of constants) the first figure is 1.23;
+// with the Gram block warmed into the L2 it does not change.
+__device__ __forceinline__ float lane_read(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+__device__ __forceinline__ float first_lane(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+// Lanes 32-63 of a and lanes 0-31 of b trade places; odd rows (of 16 lanes) of
+// a and even rows of b trade places.
+__device__ __forceinline__ void swap32(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor8 = 0x128;
+
+// Sums of a and of b over the wave (fixed order), in every lane.
+__device__ __forceinline__ void wave_sum2_fold(float& a, float& b) {
+  swap32(a, b);
+  float v = a + b;            // lanes 0-31: a, lanes 32-63: b
+  asm volatile(
+      "s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+      "s_nop 1"
+      : "+v"(v));
+  a = lane_read(v, 31);
+  b = lane_read(v, 63);
+}
+
+// acc, accb += w[i] h[i] for even and odd i < 16, two chains; lane i of every row
+// of 16 lanes holds w[i], which the FMA broadcasts over the row (DPP).  The
+// compiler folds no such broadcast into an FMA by itself; the nop covers the
+// hazard of a vector write before a DPP read.
+__device__ __forceinline__ void row_fma16(float& acc, float& accb, float w, const float (&h)[16]) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f32_dpp %0, %2, %3 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %2, %4 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %2, %5 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %2, %6 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %2, %7 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %2, %8 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %2, %9 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %2, %10 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %2, %11 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %2, %12 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %2, %13 row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %2, %14 row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %2, %15 row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %2, %16 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %2, %17 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %2, %18 row_newbcast:15 row_mask:0xf bank_mask:0xf"
+      : "+v"(acc), "+v"(accb)
+      : "v"(w), "v"(h[0]), "v"(h[1]), "v"(h[2]), "v"(h[3]), "v"(h[4]), "v"(h[5]), "v"(h[6]), "v"(h[7]),
+        "v"(h[8]), "v"(h[9]), "v"(h[10]), "v"(h[11]), "v"(h[12]), "v"(h[13]), "v"(h[14]), "v"(h[15]));
+}
+
+template <int V>
+using int_c = std::integral_constant<int, V>;
+
+template <int NSEG, bool SEC, bool TRACE, bool TRAJ>
+__global__ __launch_bounds__(512) void select_seq_kernel(SelParams p) {
+  constexpr int HX = 64 * NSEG;                         // history entries of a second column
+  __shared__ __attribute__((aligned(16))) float hx[SEC ? 8 * 2 * HX * 4 : 4];   // [wave][half][entry][4]
+  // row stride 20 floats: 16 consecutive rows' 16-byte pieces fall on different banks
+  __shared__ __attribute__((aligned(16))) float hopen[512 * 20];
+  __shared__ float2 slot[2][8];                         // a wave's best (value, column), by step parity
+  __shared__ float4 red[2][8];                          // TRACE: best, its column, runner-up
+  __shared__ float zpart[2][8];                         // TRAJ: partial softmax sums
+  __shared__ int cnt[16];
+  const int g = blockIdx.x;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int W = SEC ? 8 : p.W;
+
+  const int g0 = p.grp_off[g];
+  const int n = p.grp_off[g + 1] - g0;
+  const int cap = p.grp_cap[g];
+  if (!group_valid(p, g, 1, tid)) return;
+  const bool full = (p.flags & SP_FULL_ROLLOUT) != 0;   // STOP scored, never taken while tokens remain
+
+  const int ld = p.ld;
+  const float* A = p.gram + (int64_t)g * p.gstride;          // A row r at A + r * ld
+  const float* Bm = A + (int64_t)(n + 1) * ld;               // B row r at Bm + r * ld
+  const float* CK = A + (int64_t)(2 * n + 2) * ld;           // the three parts of cK
+  const int j = tid;
+  const bool mcol = j < n;
+  const int js = 512 + (wave << 3) + (lane >> 3);            // second column (eight lanes each)
+  const bool scol = SEC && js < n;
+  const int jc = mcol ? j : 0, jsc = scol ? js : 0;   // columns a lane reads (0 when it has none)
+  const float sigma = p.sigma, c1 = p.c1;
+
+  auto ckv = [&](int c) { return (CK[c] + CK[ld + c]) + CK[2 * ld + c]; };
+  const float ck_main = mcol ? ckv(j) : 0.0f;
+  const float ck_sec = scol ? ckv(js) : 0.0f;
+  const float ck_stop = ckv(n);
+
+  if (SEC)
+    for (int i = tid; i < 8 * 2 * HX; i += 512)
+      reinterpret_cast<float4*>(hx)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (tid < 16) slot[tid >> 3][tid & 7] = make_float2(-INFINITY, __int_as_float(-1));
+  float* hxw = hx + (SEC ? wave * 2 * HX * 4 : 0);
+
+  // History B values of column j: whole blocks of 16 entries in registers, the
+  // open block in LDS (this thread's own row of hopen, zero past the history).
+  float h[4 * NSEG][16];
+  float* hop = hopen + 20 * tid;
+#pragma unroll
+  for (int i = 0; i < 16; i += 4) *reinterpret_cast<float4*>(hop + i) = make_float4(0.f, 0.f, 0.f, 0.f);
+  // Lane i of segment k is entry 64 k + i: its column's byte offset in a row, its
+  // B value of STOP (zero until the entry is stored), its score for this step.
+  uint32_t hc[NSEG + 1];
+  float sh[NSEG + 1], r[NSEG + 1];
+#pragma unroll
+  for (int k = 0; k <= NSEG; ++k) {
+    hc[k] = 0;
+    sh[k] = r[k] = 0.0f;
+  }
+  // the newest entry: A and B values, B stored into the history after its step
+  float a_main, a_sec = 0.0f, a_stop, b_main, b_sec = 0.0f, b_stop;
+
+  // Entry `pos` becomes the newest: every load of the step at once, the scores
+  // first.  It lies in segment S, or (EDGE, S + 1 being pos / 64) opens the next.
+  auto issue = [&](auto s_c, auto edge_c, int row, int col, int pos, float& na, float& nas, float& nast,
+                   float& nb, float& nbs, float& nbst) {
+    constexpr int S = decltype(s_c)::value, SN = decltype(edge_c)::value ? S + 1 : S;
+    const int at = pos - 64 * S;
+#pragma unroll
+    for (int k = S; k <= SN; ++k) hc[k] = lane + 64 * (k - S) == at ? 4u * (uint32_t)col : hc[k];
+    const char* Ar = reinterpret_cast<const char*>(A + (int64_t)row * ld);
+    const char* Br = reinterpret_cast<const char*>(Bm + (int64_t)row * ld);
+#pragma unroll
+    for (int k = 0; k <= SN; ++k) r[k] = *reinterpret_cast<const float*>(Ar + hc[k]);
+    na = *reinterpret_cast<const float*>(Ar + 4u * (uint32_t)jc);
+    if (SEC) nas = *reinterpret_cast<const float*>(Ar + 4u * (uint32_t)jsc);
+    nast = *reinterpret_cast<const float*>(Ar + 4u * (uint32_t)n);
+    nb = *reinterpret_cast<const float*>(Br + 4u * (uint32_t)jc);
+    if (SEC) nbs = *reinterpret_cast<const float*>(Br + 4u * (uint32_t)jsc);
+    nbst = *reinterpret_cast<const float*>(Br + 4u * (uint32_t)n);
+  };
+  issue(int_c<0>{}, int_c<0>{}, n, n + 1, 0, a_main, a_sec, a_stop, b_main, b_sec, b_stop);   // START
+  lds_barrier();
+  bool valid = mcol, valid_sec = scol;      // still to be taken
+  int kept = 0;
+
+  // Trajectory sums: step t's unnormalised candidate weights stay in registers
+  // while the per-wave partial sums cross the step's barrier; at the top of the
+  // next step every lane adds the partials in wave order.
+  const bool traj = TRAJ;
+  float tj_A = 1.0f, tj_bt = 1.0f, tj_kbar = 0.0f, tj_s = 0.0f, tj_s2 = 0.0f;
+  float tj_e = 0.0f, tj_e2 = 0.0f, tj_estop = 0.0f;
+  int tj_t = 0;
+  auto traj_finish = [&]() {
+    const int pp = tj_t & 1;
+    float Z = tj_estop;
+    for (int w = 0; w < W; ++w) Z += zpart[pp][w];
+    const float inv = Z > 0.0f ? 1.0f / Z : 0.0f;
+    const float pst = Z > 0.0f ? tj_estop * inv : 1.0f;   // no finite candidate: p(STOP) = 1
+    tj_bt *= p.traj_beta;                                   // beta^t
+    const float wgt = tj_A * tj_bt * inv;
+    tj_s = fmaf(wgt, tj_e, tj_s);
+    if (SEC) tj_s2 = fmaf(wgt, tj_e2, tj_s2);
+    tj_kbar = fmaf(tj_A, 1.0f - pst, tj_kbar);
+    if (tid == 0 && p.traj_pstop && tj_t <= p.traj_pstop_steps)
+      p.traj_pstop[(int64_t)g * p.traj_pstop_steps + (tj_t - 1)] = pst;
+    tj_A *= 1.0f - pst;
+    tj_t = 0;
+  };
+
+  // Step t, whose newest entry t - 1 lies in block BK of 16 entries (segment S;
+  // S = NSEG: one entry past the last block).  True when the episode ends.
+  auto step = [&](auto bk_c, int t) -> bool {
+    constexpr int BK = decltype(bk_c)::value, S = BK / 4, ROW = BK % 4;
+    const int pl = (t - 1) - 64 * S;         // the newest entry's lane
+    const int par = t & 1;
+    if (traj && tj_t) traj_finish();
+
+    // ---- history softmax, by every wave
+    float e[S + 1];
+    float m = lane <= pl ? r[S] * c1 : -INFINITY;
+#pragma unroll
+    for (int k = 0; k < S; ++k) m = fmaxf(m, r[k] * c1);
+    m = wave_max_fused(m);
+    float sum = 0.0f, s2 = 0.0f;
+#pragma unroll
+    for (int k = 0; k <= S; ++k) {
+      const float x = __builtin_amdgcn_exp2f(fmaf(r[k], c1, -m));
+      e[k] = k < S || lane <= pl ? x : 0.0f;
+      sum += e[k];
+      if (k < NSEG) s2 = fmaf(e[k], sh[k], s2);
+    }
+    wave_sum2_fold(sum, s2);
+    const float inv = __builtin_amdgcn_rcpf(sum);
+    const float e_new = lane_read(e[S], pl);
+
+    // ---- second columns: the lane's entries for the wave's eight columns
+    float qs = 0.0f;
+    if (SEC) {
+      float v[8];
+#pragma unroll
+      for (int k = 0; k <= (S < NSEG ? S : NSEG - 1); ++k) {
+        const float4 x = reinterpret_cast<const float4*>(hxw)[64 * k + lane];
+        const float4 y = reinterpret_cast<const float4*>(hxw)[HX + 64 * k + lane];
+        const float q[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v[c] = k == 0 ? e[k] * q[c] : fmaf(e[k], q[c], v[c]);
+      }
+      // lanes 32 apart, rows 16 apart, then the row: column lane / 8
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        swap32(v[c], v[c + 4]);
+        v[c] += v[c + 4];
+      }
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        swap16(v[c], v[c + 2]);
+        v[c] += v[c + 2];
+      }
+      const float u0 = v[0] + dpp<kDppRor8>(v[0]), u1 = v[1] + dpp<kDppRor8>(v[1]);
+      qs = (lane & 8) ? u1 : u0;
+      qs += dpp<kDppXor1>(qs);
+      qs += dpp<kDppXor2>(qs);
+      qs += dpp<kDppHalfMirror>(qs);
+      qs = fmaf(e_new, b_sec, qs);
+    }
+
+    // ---- the lane's column: older entries (the newest one's register still
+    // holds zero), then the newest
+    float acc = 0.0f, accb = 0.0f;
+    auto seg_sum = [&](auto k_c) {
+      constexpr int k = decltype(k_c)::value;
+      if constexpr (k <= S && k < NSEG) {
+        float w[4] = {e[k], 0.0f, e[k], 0.0f};
+        swap32(w[0], w[2]);                    // rows 0 1 0 1 and 2 3 2 3
+        w[1] = w[0];
+        w[3] = w[2];
+        swap16(w[0], w[1]);                    // row 0, row 1
+        swap16(w[2], w[3]);                    // row 2, row 3
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (4 * k + q < BK) {
+            row_fma16(acc, accb, w[q], h[4 * k + q]);
+          } else if (4 * k + q == BK) {
+            float o[16];
+#pragma unroll
+            for (int i = 0; i < 16; i += 4) {
+              const float4 x = *reinterpret_cast<const float4*>(hop + i);
+              o[i] = x.x;
+              o[i + 1] = x.y;
+              o[i + 2] = x.z;
+              o[i + 3] = x.w;
+            }
+            row_fma16(acc, accb, w[q], o);
+          }
+        }
+      }
+    };
+    seg_sum(int_c<0>{});
+    seg_sum(int_c<1>{});
+    seg_sum(int_c<2>{});
+    acc = fmaf(e_new, b_main, acc + accb);
+    const float lj = sigma * (ck_main + a_main + acc * inv);
+    const float l_stop = sigma * (ck_stop + a_stop + fmaf(e_new, b_stop, s2) * inv) + p.b_stop;
+    const float v = valid ? lj : -INFINITY;
+    float ls = -INFINITY;
+    if (SEC) ls = valid_sec ? sigma * (ck_sec + a_sec + qs * inv) : -INFINITY;
+
+    if (TRACE && p.logit_n > 0 && t <= p.trace_steps) {
+      float* lrec = p.trace + ((int64_t)g * p.trace_steps + (t - 1)) * p.trace_w + p.logit_off;
+      if (mcol) lrec[j] = v;
+      if (scol && (lane & 7) == 0) lrec[js] = ls;
+      if (tid == 0) lrec[p.logit_n] = l_stop;
+    }
+
+    // ---- this wave's best candidate (lowest column on ties) into its slot
+    const float wbest = wave_max_fused(SEC ? fmaxf(v, ls) : v);
+    int wcol = -1;
+    if (wbest > -INFINITY) {
+      const uint64_t m1 = __ballot(v == wbest);
+      wcol = (wave << 6) + __ffsll((unsigned long long)m1) - 1;
+      if (SEC && !m1)
+        wcol = 512 + (wave << 3) + ((__ffsll((unsigned long long)__ballot(ls == wbest)) - 1) >> 3);
+    }
+    if (lane == 0) slot[par][wave] = make_float2(wbest, __int_as_float(wcol));
+    if (TRACE) {
+      // runner-up of this wave: the best candidate other than wcol
+      const float w1 = j != wcol ? v : -INFINITY;
+      const float w2 = SEC && js != wcol ? ls : -INFINITY;
+      const float v2 = wave_max_fused(fmaxf(w1, w2));
+      if (lane == 0) red[par][wave] = make_float4(wbest, __int_as_float(wcol), v2, 0.0f);
+    }
+    lds_barrier();
+
+    // ---- the decision, by every wave: the largest slot, lowest column on ties
+    const float2 s = slot[par][lane & 7];
+    float best = s.x;
+    best = fmaxf(best, dpp<kDppXor1>(best));
+    best = fmaxf(best, dpp<kDppXor2>(best));
+    best = first_lane(fmaxf(best, dpp<kDppHalfMirror>(best)));
+    int a = n;                                 // STOP, also when no finite candidate is left
+    if (best > -INFINITY && (full || !(first_lane(l_stop) > best))) {
+      uint32_t who = (uint32_t)__ballot(s.x == best) & 0xffu;
+      a = __builtin_amdgcn_readlane(__float_as_int(s.y), __ffs(who) - 1);
+      for (who &= who - 1; who; who &= who - 1) {
+        const int o = __builtin_amdgcn_readlane(__float_as_int(s.y), __ffs(who) - 1);
+        a = o < a ? o : a;
+      }
+    }
+    if (TRACE && tid == 0 && t <= p.trace_steps) {
+      float r2 = a == n ? -INFINITY : l_stop;
+      for (int w = 0; w < W; ++w) {
+        const float4 q = red[par][w];
+        r2 = fmaxf(r2, __float_as_int(q.y) == a ? q.z : q.x);
+      }
+      float* rec = p.trace + ((int64_t)g * p.trace_steps + (t - 1)) * p.trace_w;
+      rec[0] = __int_as_float(a == n ? -1 : a);
+      rec[1] = a == n ? l_stop : best;
+      rec[2] = r2;
+      rec[3] = l_stop;
+    }
+    if (traj) {
+      // this step's candidate weights (the taken token is still a candidate)
+      const float M = best > l_stop ? best : l_stop;
+      const bool any = M > -INFINITY;
+      tj_e = any && valid ? __builtin_amdgcn_exp2f((lj - M) * p.traj_c) : 0.0f;
+      if (SEC) tj_e2 = any && ls > -INFINITY && (lane & 7) == 0 ? __builtin_amdgcn_exp2f((ls - M) * p.traj_c) : 0.0f;
+      tj_estop = any && l_stop > -INFINITY ? __builtin_amdgcn_exp2f((l_stop - M) * p.traj_c) : 0.0f;
+      const float part = wave_sum_fused(tj_e + tj_e2);
+      if (lane == 0) zpart[par][wave] = part;
+      tj_t = t;
+    }
+    if (a == n) return true;
+    ++kept;
+    valid = valid && j != a;
+    if (SEC) valid_sec = valid_sec && js != a;
+    if constexpr (S < NSEG) {
+      // the loads of the next step, then this step's newest entry into the history
+      float na, nas = 0.0f, nast, nb, nbs = 0.0f, nbst;
+      issue(int_c<S>{}, int_c<ROW == 3>{}, a, a, t, na, nas, nast, nb, nbs, nbst);
+      hop[pl & 15] = b_main;
+      sh[S] = lane == pl ? b_stop : sh[S];
+      if (SEC && (lane & 7) == 0)
+        hxw[((lane >> 5) * HX + 64 * S + pl) * 4 + ((lane >> 3) & 3)] = b_sec;
+      a_main = na;
+      a_sec = nas;
+      a_stop = nast;
+      b_main = nb;
+      b_sec = nbs;
+      b_stop = nbst;
+    }
+    return false;
+  };
+
+  // Block by block; a full block moves from LDS to registers.
+  bool done = cap < 1;
+  int t = 1;
+  auto block = [&](auto bk_c) {
+    constexpr int BK = decltype(bk_c)::value;
+    if constexpr (BK < 4 * NSEG) {
+      for (int i = 0; i < 16 && !done; ++i, ++t) done = step(bk_c, t) || t >= cap;
+      if (done) return;
+#pragma unroll
+      for (int i = 0; i < 16; i += 4) {
+        const float4 x = *reinterpret_cast<const float4*>(hop + i);
+        h[BK][i] = x.x;
+        h[BK][i + 1] = x.y;
+        h[BK][i + 2] = x.z;
+        h[BK][i + 3] = x.w;
+        *reinterpret_cast<float4*>(hop + i) = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+    }
+  };
+  block(int_c<0>{});
+  block(int_c<1>{});
+  block(int_c<2>{});
+  block(int_c<3>{});
+  block(int_c<4>{});
+  block(int_c<5>{});
+  block(int_c<6>{});
+  block(int_c<7>{});
+  block(int_c<8>{});
+  block(int_c<9>{});
+  block(int_c<10>{});
+  block(int_c<11>{});
+  // a group of exactly 64 NSEG tokens, all taken below its cap: one more step
+  if (!done) step(int_c<4 * NSEG>{}, t);
+  __syncthreads();
+
+  // ---- native order (Algorithm 1 step 4): ascending columns, the lane-owned
+  // ones first, then the second columns (one lane of eight reports).
+  if (traj) {
+    if (tj_t) traj_finish();
+    if (mcol) p.traj_s[g0 + j] = tj_s;
+    if (scol && (lane & 7) == 0) p.traj_s[g0 + js] = tj_s2;
+    if (tid == 0) p.traj_kbar[g] = tj_kbar;
+  }
+  const uint64_t ballot = __ballot(mcol && !valid);
+  const uint64_t sb = __ballot(scol && !valid_sec && (lane & 7) == 0);
+  if (lane == 0) {
+    cnt[wave] = __popcll(ballot);
+    if (SEC) cnt[8 + wave] = __popcll(sb);
+  }
+  __syncthreads();
+  int before = 0, total = 0, before2 = 0;
+  for (int w = 0; w < W; ++w) {
+    if (w < wave) before += cnt[w];
+    total += cnt[w];
+  }
+  if (SEC)
+    for (int w = 0; w < wave; ++w) before2 += cnt[8 + w];
+  if (mcol && !valid) {
+    const int pos = before + __popcll(ballot & ((1ull << lane) - 1ull));
+    p.grp_kept[(int64_t)g * p.max_cap + pos] = j;
+  }
+  if (scol && !valid_sec && (lane & 7) == 0) {
+    const int pos = total + before2 + __popcll(sb & ((1ull << lane) - 1ull));
+    p.grp_kept[(int64_t)g * p.max_cap + pos] = js;
+  }
+  if (tid == 0) {
+    p.grp_count[g] = kept;
+    if (p.grp_cnt_out) p.grp_cnt_out[g] = kept;
+  }
+}
+
+// ------------------------------------------------------------------ the general kernel
+//
+// Several tokens a round, groups of more than 576 tokens, caps above 192, and
+// the frozen query of SP_NO_HISTORY.
+//
 // One workgroup runs one episode with W waves.  Thread j < 64 W owns
 // candidate column j: its history B values are in registers (the first RREG
 // entries), then in LDS (lt entries), then re-read from the Gram buffer.
@@ -229,24 +721,7 @@ __global__ __launch_bounds__(MAXT) void select_kernel(SelParams p) {
   const int64_t g0 = p.grp_off[g], g1 = p.grp_off[g + 1];
   const int n = (int)(g1 - g0);
   const int cap = p.grp_cap[g];
-  const int b = p.grp_img[g];
-  {
-    int code = 0;
-    if (g0 < 0 || g1 < g0 || g1 > p.T_vis || b < 0 || b >= p.B) code = SP_DEV_BAD_OFFSETS;
-    else if (n > p.max_group) code = SP_DEV_GROUP_TOO_LARGE;
-    else if (cap < 0 || (int64_t)p.max_cap <
-                          ((int64_t)cap * (GROUPED ? p.g : 1) < n ? (int64_t)cap * (GROUPED ? p.g : 1) : n))
-      code = SP_DEV_BAD_CAP;
-    else if (g0 < p.img_off[b] || g1 > p.img_off[b + 1]) code = SP_DEV_BAD_OFFSETS;
-    if (code) {
-      if (tid == 0) {
-        set_device_error(p.err, code);
-        p.grp_count[g] = 0;
-        if (p.grp_cnt_out) p.grp_cnt_out[g] = 0;
-      }
-      return;
-    }
-  }
+  if (!group_valid(p, g, GROUPED ? p.g : 1, tid)) return;
   const bool no_history = (p.flags & SP_NO_HISTORY) != 0;
   const bool full = (p.flags & SP_FULL_ROLLOUT) != 0;   // STOP scored, never taken while tokens remain
   const int lt = p.lt, ks = p.ks;
@@ -1287,9 +1762,8 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
   const bool grouped = a.g > 1;
   // grouped kernels hold the newest group's values too, and their histories
   // grow g entries a round: 64 history registers, then the LDS tier
-  int rreg = wide ? 32 : need <= 64 || grouped ? 64 : need <= 128 ? 128 : 160;
-  // the trajectory sums take registers too: at most 128 history registers
-  if (a.traj_s && rreg > 128) rreg = 128;
+  // (one token a round: 160, or 128 beside the trajectory sums)
+  const int rreg = wide ? 32 : grouped ? 64 : a.traj_s ? 128 : 160;
   p.W = W;
   p.hcap = (int)align_up((size_t)need + 1, 4);
   // alpha covers the register blocks' prefetch (up to rreg) and the second
@@ -1297,6 +1771,27 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
   p.alpha_ld = (int)align_up((size_t)(need > rreg ? need : rreg), sec ? 64 : 16);
   p.sigma = 1.0f / sqrtf((float)a.h);
   p.c1 = p.sigma * 1.4426950408889634f;
+  const void* fn = nullptr;
+  size_t lds = 0;
+  // One token a round, up to 576 tokens and 193 history entries (START, and a
+  // token a round up to a cap of 192): the history fits the registers.  The
+  // frozen query of SP_NO_HISTORY (a diagnostic) has no history to keep.
+  const int nseg = (need + 62) / 64;                  // 64 nseg + 1 entries
+  const bool seq = !grouped && !wide && nseg <= 3 && !(a.flags & SP_NO_HISTORY);
+  if (seq) {
+#define SP_PICK_SEQ(NSEG, SEC)                                                           \
+  if (nseg == NSEG && sec == SEC) {                                                      \
+    if (traj)                                                                            \
+      fn = trace ? (const void*)select_seq_kernel<NSEG, SEC, true, true>                 \
+                 : (const void*)select_seq_kernel<NSEG, SEC, false, true>;               \
+    else                                                                                 \
+      fn = trace ? (const void*)select_seq_kernel<NSEG, SEC, true, false>                \
+                 : (const void*)select_seq_kernel<NSEG, SEC, false, false>;              \
+  }
+    SP_PICK_SEQ(1, false) SP_PICK_SEQ(2, false) SP_PICK_SEQ(3, false)
+    SP_PICK_SEQ(1, true) SP_PICK_SEQ(2, true) SP_PICK_SEQ(3, true)
+#undef SP_PICK_SEQ
+  } else {
   // LDS: fixed arrays, then wave 0's second-column history (all of it if it
   // fits), then the lane-owned tier past the registers; entries beyond either
   // are read again from the Gram buffer.
@@ -1322,37 +1817,28 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
   }
   p.lt = lt;
   p.ks = ks;
-  const size_t lds = (size_t)SelLds(W, lt, ks, p.alpha_ld, p.hcap, copies).total;
+  lds = (size_t)SelLds(W, lt, ks, p.alpha_ld, p.hcap, copies).total;
   if (lds > (size_t)kLdsBytes) return hipErrorInvalidValue;
 
-  const void* fn = nullptr;
-#define SP_PICK(RR, SEC, MAXT)                                                           \
-  if (!grouped && rreg == RR && sec == SEC && (MAXT == 1024) == wide) {                  \
-    if (traj)                                                                            \
-      fn = trace ? (const void*)select_kernel<RR, SEC, true, MAXT, 1, true>              \
-                 : (const void*)select_kernel<RR, SEC, false, MAXT, 1, true>;            \
-    else                                                                                 \
-      fn = trace ? (const void*)select_kernel<RR, SEC, true, MAXT, 1, false>             \
-                 : (const void*)select_kernel<RR, SEC, false, MAXT, 1, false>;           \
-  }
-#define SP_PICK_NT(RR, SEC, MAXT)                                                        \
-  if (!grouped && rreg == RR && sec == SEC && (MAXT == 1024) == wide && !traj)           \
-    fn = trace ? (const void*)select_kernel<RR, SEC, true, MAXT, 1, false>               \
-               : (const void*)select_kernel<RR, SEC, false, MAXT, 1, false>;
-  SP_PICK(64, false, 512) SP_PICK(128, false, 512) SP_PICK_NT(160, false, 512)
-  SP_PICK(64, true, 512) SP_PICK(128, true, 512) SP_PICK_NT(160, true, 512)
-  SP_PICK(32, false, 1024)
+#define SP_PICK(RR, SEC, MAXT, TRAJ)                                                     \
+  if (!grouped && rreg == RR && sec == SEC && (MAXT == 1024) == wide && traj == TRAJ)    \
+    fn = trace ? (const void*)select_kernel<RR, SEC, true, MAXT, 1, TRAJ>                \
+               : (const void*)select_kernel<RR, SEC, false, MAXT, 1, TRAJ>;
+  SP_PICK(160, false, 512, false) SP_PICK(160, true, 512, false)
+  SP_PICK(128, false, 512, true) SP_PICK(128, true, 512, true)
+  SP_PICK(32, false, 1024, false) SP_PICK(32, false, 1024, true)
 #undef SP_PICK
-#undef SP_PICK_NT
 #define SP_PICK_G(RR, SEC, MAXT)                                                         \
   if (grouped && rreg == RR && sec == SEC && (MAXT == 1024) == wide)                     \
     fn = trace ? (const void*)select_kernel<RR, SEC, true, MAXT, kGMax, false>           \
                : (const void*)select_kernel<RR, SEC, false, MAXT, kGMax, false>;
   SP_PICK_G(64, false, 512) SP_PICK_G(64, true, 512) SP_PICK_G(32, false, 1024)
 #undef SP_PICK_G
+  }
   if (!fn) return hipErrorInvalidValue;
   record_event(a.events, 2, stream);
-  if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess)
+  if (lds > 0 &&
+      (e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess)
     return e;
   void* kargs[] = {&p};
   if ((e = hipLaunchKernel(fn, dim3(a.G), dim3(64 * W), kargs, lds, stream)) != hipSuccess) return e;
