@@ -87,9 +87,9 @@ GateWs gate_ws_layout(const sp_dims* d, int64_t T) {
 
 // Header, then the encoder's buffers (sp_internal.h, EncodeArgs).
 struct EncodeWs {
-  size_t R, L, A, QKV, HID, Vt, total;
+  size_t R, L, A, QKV, HID, total;
 };
-EncodeWs encode_ws_layout(const sp_dims* d, int64_t T_vis, int64_t T_txt, int B, int max_seq) {
+EncodeWs encode_ws_layout(const sp_dims* d, int64_t T_vis, int64_t T_txt) {
   EncodeWs w;
   const size_t S = (size_t)(T_vis + T_txt), dd = (size_t)d->d;
   w.R = kWsHeaderBytes;
@@ -97,8 +97,7 @@ EncodeWs encode_ws_layout(const sp_dims* d, int64_t T_vis, int64_t T_txt, int B,
   w.A = align_up(w.L + S * dd * 2, 256);
   w.QKV = align_up(w.A + S * dd * 2, 256);
   w.HID = align_up(w.QKV + S * dd * 3 * 2, 256);
-  w.Vt = align_up(w.HID + S * dd * 4 * 2, 256);
-  w.total = align_up(w.Vt + (size_t)B * dd * encode_smax_pad(max_seq) * 2, 256);
+  w.total = align_up(w.HID + S * dd * 4 * 2, 256);
   return w;
 }
 
@@ -146,7 +145,7 @@ size_t stepprune_workspace_bytes(int32_t which, const sp_dims* dims, int64_t T_v
       return gate_ws_layout(dims, T_vis).total;
     case 4:
       if (check_encode_dims(dims) != SP_OK || B < 1 || max_group < 1) return 0;
-      return encode_ws_layout(dims, T_vis, T_txt, B, max_group).total;
+      return encode_ws_layout(dims, T_vis, T_txt).total;
   }
   return 0;
 }
@@ -436,7 +435,7 @@ sp_status stepprune_encode(const sp_dims* dims, const void* X, int64_t T_vis,
     for (const void* q : ptrs)
       if (!q || !aligned16(q)) return SP_EINVAL;
   }
-  const EncodeWs w = encode_ws_layout(dims, T_vis, T_txt, B, max_seq);
+  const EncodeWs w = encode_ws_layout(dims, T_vis, T_txt);
   if (ws_bytes < w.total) return SP_EWORKSPACE;
   char* base = static_cast<char*>(ws);
   EncodeArgs a;
@@ -475,7 +474,6 @@ sp_status stepprune_encode(const sp_dims* dims, const void* X, int64_t T_vis,
   a.A = reinterpret_cast<uint16_t*>(base + w.A);
   a.QKV = reinterpret_cast<uint16_t*>(base + w.QKV);
   a.HID = reinterpret_cast<uint16_t*>(base + w.HID);
-  a.Vt = reinterpret_cast<uint16_t*>(base + w.Vt);
   a.err = reinterpret_cast<int32_t*>(base);
   record_event(events, 0, stream);
   const hipError_t e = launch_encode(a, stream);

@@ -29,14 +29,13 @@ namespace sp {
 namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef __attribute__((address_space(3))) bf16x4_t* ltr_t;
 
 constexpr int kHead = 128;                  // head width
 constexpr int kQPerWave = 32;               // queries of one wave (one 32 x 32 MFMA tile)
-constexpr int kAttnWaves = 4;               // 128 queries per workgroup
-constexpr int kKeyBlock = 32;               // keys per online-softmax step
-constexpr int kKeyTile = 64;                // keys per LDS tile of K and V^T
-constexpr int kVtKeys = 64;                 // keys per transpose tile
+constexpr int kAttnWaves = 4;               // waves of an attention workgroup
 constexpr float kTextLnEps = 1e-5f;
 
 // The image owning row r of a packed array with offsets off[0..B]: the last
@@ -182,96 +181,105 @@ __global__ __launch_bounds__(256) void enc_out_kernel(
 
 // ---------------------------------------------------------------- attention
 
-// Vt[b][head][e][p] = V[so_b + k][128 head + e] for k < S_b, 0 up to smax_pad:
-// each head's values transposed, keys contiguous except that the middle two
-// 4-key quarters of every 16 keys trade places (position p of key k: quarter
-// order 0, 2, 1, 3).  The attention's value operand for a lane half is then
-// one 16-byte chunk (see attn_kernel).  One workgroup per 64 keys x 128.
-__global__ __launch_bounds__(256) void vt_kernel(
-    const uint16_t* __restrict__ QKV, int d, int smax_pad, const int32_t* __restrict__ img_off,
-    const int32_t* __restrict__ text_off, int max_seq, int64_t S_total, uint16_t* __restrict__ Vt,
-    int32_t* err) {
-  const int b = blockIdx.z, hd = blockIdx.y, heads = gridDim.y;
-  const int k0 = blockIdx.x * kVtKeys;
-  int64_t so;
-  int S;
-  if (!sequence_of(img_off, text_off, b, max_seq, S_total, so, S, err, false)) return;
-  __shared__ __attribute__((aligned(16))) uint16_t tile[kVtKeys][kHead + 8];
-  const int tid = threadIdx.x;
-  const int64_t ld = 3 * (int64_t)d;
-  for (int i = tid; i < kVtKeys * (kHead / 8); i += 256) {
-    const int r = i / (kHead / 8), ch = i % (kHead / 8);
-    const int k = k0 + r;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (k < S) v = *reinterpret_cast<const uint4*>(QKV + (so + k) * ld + 2 * d + hd * kHead + 8 * ch);
-    *reinterpret_cast<uint4*>(&tile[r][8 * ch]) = v;
-  }
-  __syncthreads();
-  const int e = tid >> 1, kh = tid & 1;
-  uint16_t* dst = Vt + (((int64_t)b * heads + hd) * kHead + e) * smax_pad + k0 + 32 * kh;
-#pragma unroll
-  for (int j = 0; j < 32; j += 16) {
-    const uint16_t* c = &tile[32 * kh + j][e];
-    auto two = [&](int k) {
-      return (uint32_t)c[k * (kHead + 8)] | ((uint32_t)c[(k + 1) * (kHead + 8)] << 16);
-    };
-    // positions 0-7: keys 0-3, 8-11; positions 8-15: keys 4-7, 12-15
-    *reinterpret_cast<uint4*>(dst + j) = make_uint4(two(0), two(2), two(8), two(10));
-    *reinterpret_cast<uint4*>(dst + j + 8) = make_uint4(two(4), two(6), two(12), two(14));
-  }
-}
-
 __device__ __forceinline__ bf16x8_t ld16(const uint16_t* p) {
   return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(p));
 }
-__device__ __forceinline__ bf16x8_t pack8(const float* v) {
-  uint4 u;
-  u.x = (uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16);
-  u.y = (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16);
-  u.z = (uint32_t)f32_to_bf16(v[4]) | ((uint32_t)f32_to_bf16(v[5]) << 16);
-  u.w = (uint32_t)f32_to_bf16(v[6]) | ((uint32_t)f32_to_bf16(v[7]) << 16);
-  return __builtin_bit_cast(bf16x8_t, u);
+
+// The larger of v in this lane and in the lane 32 away (their sum likewise).
+__device__ __forceinline__ float half_max(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float half_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // Multi-head attention of every image's sequence: O[so + q][128 h + e] =
 // sum_k softmax_k(q . k / sqrt(128)) v[k][e], over the image's keys (causal:
-// keys k <= q).  Grid (query blocks of 128, heads, images); a wave takes 32
-// queries and walks the keys 32 at a time with an online softmax:
+// keys k <= q).  A wave takes 32 queries and walks keys in steps of 32 or 64
+// with an online softmax:
 //   S^T = K Q^T on the matrix cores (v_mfma_f32_32x32x16_bf16: K as the row
 //   operand, Q as the column operand), so lane l holds query q0 + l % 32 and
-//   16 of the block's 32 keys (key 8 (r / 4) + 4 (l / 32) + r % 4 in register
-//   r); a query's maximum and sum need its lane and the lane 32 away;
-//   O^T += V^T P: the probabilities a lane holds are its half of the
-//   operand's k slots as they stand (slot 8 (l / 32) + j is key 4 (l / 32) + j
-//   for j < 4 and 8 + 4 (l / 32) + j - 4 for j >= 4, plus 16 for the second
-//   16 keys), which is the order vt_kernel stores the values in.
-// The workgroup's four waves share the keys and values: 64-key tiles of K
-// (64 x 128) and V^T (128 x 64) pass through LDS, two tiles deep, the next
-// tile loading straight into LDS while the current one is used.
-// LDS rows are 16-byte chunks XOR-swizzled so that each 16-lane pass of a
-// fragment read touches every bank once.
-// Probabilities enter the products rounded to bfloat16; the running maximum
-// rescales the partial sums in float32.
-__global__ __launch_bounds__(64 * kAttnWaves) void attn_kernel(
-    const uint16_t* __restrict__ QKV, const uint16_t* __restrict__ Vt, int d, int smax_pad,
-    const int32_t* __restrict__ img_off, const int32_t* __restrict__ text_off, int max_seq,
-    int64_t S_total, int causal, float c2, uint16_t* __restrict__ O, int32_t* err) {
-  constexpr int kTileBytes = kKeyTile * kHead * 2;                 // one K or V^T tile, 16 KB
-  __shared__ __attribute__((aligned(16))) char smem[2][2][kTileBytes];   // [buffer][K, V^T]
-  const int b = blockIdx.z, hd = blockIdx.y, heads = gridDim.y;
+//   16 of each 32 keys (key 8 (r / 4) + 4 (l / 32) + r % 4 in register r); a
+//   query's maximum and sum need its lane and the lane 32 away;
+//   O^T += V^T P: the probabilities a lane holds are its half of the operand's
+//   k slots as they stand (slot 8 (l / 32) + j is key 4 (l / 32) + j for j < 4
+//   and 8 + 4 (l / 32) + j - 4 for j >= 4, plus 16 for the second 16 keys).
+//   The value operand is read from the row-major tile by the transposing LDS
+//   read (ds_read_b64_tr_b16): 16 lanes read 4 keys x 16 columns, four values
+//   of one key each, and lane i receives column i of the four keys.
+// Tiles of K and V pass through LDS two deep, the next one loading straight
+// into LDS while the current one is used.  Rows of 256 bytes are 16-byte
+// chunks, XOR-swizzled so that a pass of a fragment read touches every bank
+// once: by the row's low four bits (K), by its low two bits on 64-byte pieces
+// (V, read 64 bytes of four rows at a time).  Keys past the sequence read its
+// last row and are masked.
+//
+// Two splits of the work over a workgroup's four waves:
+//   kShared (SPLIT = false): 128 queries, 32 a wave; the waves share tiles of 64 keys.
+//   kSplit (SPLIT = true): 32 queries; each wave takes every fourth 32-key block through
+//            tiles of its own (no barrier), and the partial sums are combined
+//            through LDS at the end.
+//
+// What bounds it: with 2 x 8 matrix instructions a 32-key block, the softmax's
+// vector instructions (16 exponentials a lane).  So masks are applied only to
+// the steps that need them, the running maximum moves (and the sums are
+// rescaled) only when a step's maximum exceeds it by more than 2^8, which
+// float32 sums hold with the same relative error, and the row sums stay
+// per lane until the end.  Probabilities enter the products rounded to bfloat16.
+//
+// us at width 4096 (32 heads) against a kernel with masks, a rescale and
+// shuffles at every step, values transposed by a kernel before it, and 128
+// queries a workgroup only: 16 sequences of 640 rows 246 + 50 -> 140 (0.77
+// PFLOP/s); one of 1077 rows at width 1024, causal, 50 + 5 -> 17.
+constexpr float kRescale = 8.0f;            // log2 of the largest unscaled probability
+
+template <bool SPLIT>
+struct AttnShape {
+  static constexpr int QUERIES = SPLIT ? kQPerWave : kQPerWave * kAttnWaves;   // of a workgroup
+  static constexpr int TILE = SPLIT ? 32 * kAttnWaves : 64;                    // keys of a tile
+  static constexpr int BLOCKS = SPLIT ? 1 : 2;                                 // 32-key blocks of a step
+  static constexpr int TILE_BYTES = TILE * kHead * 2;                          // K or V
+  static constexpr int LDS = 4 * TILE_BYTES;
+  static constexpr int LOADS = TILE / 4 / kAttnWaves;                          // 4-row groups per wave
+};
+// kSplit's partial sums, over the tiles: 32 rows of 128 values a wave, padded
+constexpr int kPartRow = kHead + 4;
+static_assert(kAttnWaves * kQPerWave * (kPartRow + 2) * 4 <= AttnShape<true>::LDS, "partial sums fit the tiles");
+
+template <bool SPLIT>
+__global__ __launch_bounds__(64 * kAttnWaves, SPLIT ? 1 : 2) void attn_kernel(
+    const uint16_t* __restrict__ QKV, int d, int q_blocks, const int32_t* __restrict__ img_off,
+    const int32_t* __restrict__ text_off, int max_seq, int64_t S_total, int causal, float c2,
+    uint16_t* __restrict__ O, int32_t* err) {
+  using G = AttnShape<SPLIT>;
+  constexpr int NB = G::BLOCKS;
+  __shared__ __attribute__((aligned(1024))) char smem[G::LDS];   // [buffer][K, V]
+  const int b = blockIdx.y, heads = d / kHead;
+  // Workgroup w runs on XCD w % 8: where the heads divide over the XCDs, a
+  // head's query blocks follow one another on one of them and share its keys
+  // and values in that L2.  Causal: the blocks with the most keys come first.
+  const int w = blockIdx.x;
+  int hd, qb;
+  if (heads % 8 == 0) {
+    hd = w % 8 + 8 * (w / 8 / q_blocks);
+    qb = w / 8 % q_blocks;
+  } else {
+    hd = w / q_blocks;
+    qb = w % q_blocks;
+  }
+  if (causal) qb = q_blocks - 1 - qb;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int64_t so;
   int S;
-  const bool report = tid == 0 && blockIdx.x == 0 && hd == 0;
-  if (!sequence_of(img_off, text_off, b, max_seq, S_total, so, S, err, report)) return;
-  const int qw = blockIdx.x * (kQPerWave * kAttnWaves);            // the workgroup's first query
+  if (!sequence_of(img_off, text_off, b, max_seq, S_total, so, S, err, tid == 0 && w == 0)) return;
+  const int qw = qb * G::QUERIES;                                   // the workgroup's first query
   if (qw >= S) return;
-  const int q0 = qw + wave * kQPerWave;                             // this wave's (may be past S)
+  const int q0 = SPLIT ? qw : qw + wave * kQPerWave;                // this wave's (may be past S)
   const int ql = lane & 31, half = lane >> 5;
   const int64_t ld = 3 * (int64_t)d;
   const uint16_t* Qb = QKV + so * ld + hd * kHead;
-  const uint16_t* Kb = Qb + d;
-  const uint16_t* Vb = Vt + ((int64_t)b * heads + hd) * kHead * (int64_t)smax_pad;
   const int q = q0 + ql;
   const int qr = q < S ? q : S - 1;           // queries past the sequence compute on its last row
   bf16x8_t qf[kHead / 16];
@@ -279,43 +287,44 @@ __global__ __launch_bounds__(64 * kAttnWaves) void attn_kernel(
   for (int s = 0; s < kHead / 16; ++s) qf[s] = ld16(Qb + qr * ld + 16 * s + 8 * half);
 
   // keys the workgroup needs, and this wave's own limit
-  const int kend_wg = causal ? (S < qw + kQPerWave * kAttnWaves ? S : qw + kQPerWave * kAttnWaves) : S;
+  const int kend_wg = causal ? (S < qw + G::QUERIES ? S : qw + G::QUERIES) : S;
   // (a wave past the sequence only helps load the tiles)
   const int kend = q0 >= S ? 0 : causal ? (S < q0 + kQPerWave ? S : q0 + kQPerWave) : S;
-  const int tiles = (kend_wg + kKeyTile - 1) / kKeyTile;
+  const int tiles = (kend_wg + G::TILE - 1) / G::TILE;
 
-  // Tile loads, straight into LDS: a load instruction fills 1 KB, 4 rows of
-  // the K tile (row group w + 4 i of wave w) or 8 rows of the V^T tile; lane
-  // i lands on chunk i % 16 (i % 8) of its row, so it fetches the logical
-  // chunk that the swizzle puts there.  K rows past the sequence read its last
-  // key (masked below); V^T keys past the sequence are zero in Vt up to
-  // smax_pad.
-  static_assert(kKeyTile * kHead * 2 / 1024 == 4 * kAttnWaves, "four row groups per wave");
-  static_assert(kVtKeys % kKeyTile == 0, "V^T rows are padded to whole key tiles");
+  // Tile loads: an instruction fills 1 KB, 4 rows; lane i lands on chunk i % 16
+  // of row i / 16, so it fetches the logical chunk that the swizzle puts there.
+  // kSplit: the wave's own 32 rows; kShared: row groups wave, wave + 4, ...
+  const int lrow = lane >> 4, lch = lane & 15;
   auto issue_tile = [&](int kt, int buf) {
+    const int k0 = kt * G::TILE;
+    const uint64_t p = (uint64_t)(Qb + (int64_t)k0 * ld + d);        // uniform: into scalar registers
+    const uint32_t plo = __builtin_amdgcn_readfirstlane((uint32_t)p);
+    const uint32_t phi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
+    const char* Kt = reinterpret_cast<const char*>(((uint64_t)phi << 32) | plo);
+    const char* Vt = Kt + 2 * (int64_t)d;
+    const int last = S - 1 - k0;
+    char* dst = smem + buf * 2 * G::TILE_BYTES;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int grp = wave + kAttnWaves * i;
-      const int r = 4 * grp + (lane >> 4), ch = (lane & 15) ^ (r & 15);
-      const int k = kt * kKeyTile + r;
-      lds_dma16(Kb + (int64_t)(k < S ? k : S - 1) * ld + 8 * ch, smem[buf][0] + grp * 1024);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int grp = wave + kAttnWaves * i;
-      const int e = 8 * grp + (lane >> 3), ch = (lane & 7) ^ ((e >> 1) & 7);
-      lds_dma16(Vb + (int64_t)e * smax_pad + kt * kKeyTile + 8 * ch, smem[buf][1] + grp * 1024);
+    for (int i = 0; i < G::LOADS; ++i) {
+      const int grp = SPLIT ? wave * G::LOADS + i : wave + kAttnWaves * i;
+      const int r = 4 * grp + lrow;
+      const uint32_t row = (uint32_t)(r < last ? r : last) * (uint32_t)(2 * ld);
+      lds_dma16(Kt, row + ((lch ^ (r & 15)) << 4), dst + grp * 1024);
+      lds_dma16(Vt, row + ((lch ^ (lrow << 2)) << 4), dst + G::TILE_BYTES + grp * 1024);
     }
   };
-  // fragment reads: K rows of key block kb (32 keys) in e-slice s; V^T rows of
-  // e-tile t at the 16-key group g of the tile
-  auto kfrag = [&](int buf, int r, int s) {
-    const int ch = 2 * s + half;
-    return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(smem[buf][0] + r * 256 + ((ch ^ (r & 15)) << 4)));
+  // fragment reads: rows r of K in e-slice s; V^T rows of e-tile t at keys r0 + 4 half + 0..3
+  const int kbase = ql * 256, ksw = ql & 15;
+  auto kfrag = [&](const char* tile, int s) {
+    return __builtin_bit_cast(
+        bf16x8_t, *reinterpret_cast<const uint4*>(tile + kbase + (((2 * s + half) ^ ksw) << 4)));
   };
-  auto vfrag = [&](int buf, int e, int grp) {
-    const int ch = 2 * grp + half;
-    return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(smem[buf][1] + e * 128 + ((ch ^ ((e >> 1) & 7)) << 4)));
+  const int vr = (lane >> 2) & 3;
+  const int vbase = (4 * half + vr) * 256 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+  auto vread = [&](const char* tile, int t, int r0) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+        (ltr_t)(tile + vbase + ((t ^ vr) << 6) + r0 * 256));
   };
 
   f32x16_t o[kHead / 32];
@@ -323,89 +332,179 @@ __global__ __launch_bounds__(64 * kAttnWaves) void attn_kernel(
   for (int t = 0; t < kHead / 32; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[t][r] = 0.0f;
-  float m = -INFINITY, l = 0.0f;
+  float m = -INFINITY, l = 0.0f;              // of this lane's keys; m is its query's
 
-  issue_tile(0, 0);
-  wait_vmcnt<0>();
-  __syncthreads();
-  for (int kt = 0; kt < tiles; ++kt) {
-    const int buf = kt & 1;
-    // the other buffer was last read before the previous barrier
-    if (kt + 1 < tiles) issue_tile(kt + 1, buf ^ 1);
+  // One step: 32 NB keys from kb on, at row `row` of the buffer's tiles.
+  auto step = [&](int buf, int row, int kb) {
+    const char* Kt = smem + buf * 2 * G::TILE_BYTES + row * 256;
+    const char* Vt = Kt + G::TILE_BYTES;
+    f32x16_t st[NB];
 #pragma unroll
-    for (int sb = 0; sb < kKeyTile / kKeyBlock; ++sb) {
-      const int kb = kt * kKeyTile + sb * kKeyBlock;
-      if (kb >= kend) break;                  // uniform in the wave
-      f32x16_t st;
+    for (int n = 0; n < NB; ++n)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) st[r] = 0.0f;
+      for (int r = 0; r < 16; ++r) st[n][r] = 0.0f;
 #pragma unroll
-      for (int s = 0; s < kHead / 16; ++s)
-        st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag(buf, sb * kKeyBlock + ql, s), qf[s], st,
-                                                     0, 0, 0);
-      // Key kb is visible to every query of the wave (kb < S, and kb <= q0 when
-      // causal), so the block maximum is finite.
-      float x[16], bm = -INFINITY;
+    for (int s = 0; s < kHead / 16; ++s)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = kb + 8 * (r >> 2) + 4 * half + (r & 3);
-        const bool ok = key < S && (!causal || key <= q);
-        x[r] = ok ? st[r] * c2 : -INFINITY;
-        bm = fmaxf(bm, x[r]);
-      }
-      bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
-      const float mn = fmaxf(m, bm);
-      const float sc = __builtin_amdgcn_exp2f(m - mn);     // 0 on the first block
-      float p[16], ls = 0.0f;
+      for (int n = 0; n < NB; ++n)
+        st[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag(Kt + n * 32 * 256, s), qf[s], st[n], 0, 0, 0);
+    if (kb + 32 * NB > (causal && q0 + 1 < S ? q0 + 1 : S)) {
+      const int lim = causal && q + 1 < S ? q + 1 : S;     // keys below it are visible
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        p[r] = __builtin_amdgcn_exp2f(x[r] - mn);
-        ls += p[r];
-      }
-      ls += __shfl_xor(ls, 32, 64);
-      l = fmaf(l, sc, ls);
+      for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (kb + 32 * n + 8 * (r >> 2) + 4 * half + (r & 3) >= lim) st[n][r] = -INFINITY;
+    }
+    // Key kb is visible to every query of the wave (kb < S, and kb <= q0 when
+    // causal), so a step's maximum is finite.
+    float bm = st[0][0];
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) bm = fmaxf(bm, st[n][r]);
+    const float mx = half_max(bm) * c2;
+    if (__any(mx > m + kRescale)) {
+      const float mn = fmaxf(m, mx);
+      const float sc = __builtin_amdgcn_exp2f(m - mn);     // 0 on the first step
       m = mn;
+      l *= sc;
 #pragma unroll
       for (int t = 0; t < kHead / 32; ++t)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[t][r] *= sc;
-      const bf16x8_t pb0 = pack8(p), pb1 = pack8(p + 8);
+    }
 #pragma unroll
-      for (int t = 0; t < kHead / 32; ++t) {
-        o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfrag(buf, 32 * t + ql, 2 * sb), pb0, o[t], 0, 0, 0);
-        o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfrag(buf, 32 * t + ql, 2 * sb + 1), pb1, o[t], 0, 0, 0);
+    for (int n = 0; n < NB; ++n) {
+      bf16x8_t pb[2];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(st[n][r], c2, -m));
+        l += p;
+        pb[r >> 3][r & 7] = (__bf16)p;
+      }
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int t = 0; t < kHead / 32; ++t) {
+          const bf16x4_t lo = vread(Vt, t, 32 * n + 16 * g), hi = vread(Vt, t, 32 * n + 16 * g + 8);
+          const bf16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+          o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pb[g], o[t], 0, 0, 0);
+        }
+    }
+  };
+
+  issue_tile(0, 0);
+  if constexpr (SPLIT) {
+    const int row = 32 * wave;
+    for (int kt = 0; kt < tiles; ++kt) {
+      const int buf = kt & 1;
+      if (kt + 1 < tiles) {
+        wait_lgkm0();                        // this wave's reads of the other buffer
+        issue_tile(kt + 1, buf ^ 1);
+        wait_vmcnt<2 * G::LOADS>();          // tile kt has landed
+      } else {
+        wait_vmcnt<0>();
+      }
+      asm volatile("" ::: "memory");
+      const int kb = kt * G::TILE + row;
+      if (kb < kend) step(buf, row, kb);     // uniform in the wave
+    }
+  } else {
+    wait_vmcnt<0>();
+    __syncthreads();
+    for (int kt = 0; kt < tiles; ++kt) {
+      const int buf = kt & 1;
+      // the other buffer was last read before the previous barrier
+      if (kt + 1 < tiles) issue_tile(kt + 1, buf ^ 1);
+      if (kt * G::TILE < kend) step(buf, 0, kt * G::TILE);
+      wait_vmcnt<0>();                       // this wave's loads of the next tile
+      __syncthreads();
+    }
+  }
+  l = half_sum(l);
+
+  // O^T[e][q] in o[t][r]: e = 32 t + 8 (r / 4) + 4 (l / 32) + r % 4
+  if constexpr (SPLIT) {
+    float* part = reinterpret_cast<float*>(smem);                   // [wave][query][kPartRow]
+    float* ml = part + kAttnWaves * kQPerWave * kPartRow;            // [m, l][wave][query]
+    __syncthreads();                                                 // every wave is past its tiles
+#pragma unroll
+    for (int t = 0; t < kHead / 32; ++t)
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4)
+        *reinterpret_cast<float4*>(part + (wave * kQPerWave + ql) * kPartRow + 32 * t + 8 * g4 + 4 * half) =
+            make_float4(o[t][4 * g4], o[t][4 * g4 + 1], o[t][4 * g4 + 2], o[t][4 * g4 + 3]);
+    if (half == 0) {
+      ml[wave * kQPerWave + ql] = m;
+      ml[(kAttnWaves + wave) * kQPerWave + ql] = l;
+    }
+    __syncthreads();
+    const int cq = tid >> 3, e0 = (tid & 7) * 16;                    // 16 values of one query a thread
+    if (qw + cq >= S) return;
+    float M = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < kAttnWaves; ++v) M = fmaxf(M, ml[v * kQPerWave + cq]);
+    float L = 0.0f, acc[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+#pragma unroll
+    for (int v = 0; v < kAttnWaves; ++v) {
+      // a wave without keys has m = -inf and zero sums
+      const float mv = ml[v * kQPerWave + cq];
+      const float f = mv == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mv - M);
+      L = fmaf(ml[(kAttnWaves + v) * kQPerWave + cq], f, L);
+#pragma unroll
+      for (int e = 0; e < 16; e += 4) {
+        const float4 x = *reinterpret_cast<const float4*>(part + (v * kQPerWave + cq) * kPartRow + e0 + e);
+        acc[e] = fmaf(x.x, f, acc[e]);
+        acc[e + 1] = fmaf(x.y, f, acc[e + 1]);
+        acc[e + 2] = fmaf(x.z, f, acc[e + 2]);
+        acc[e + 3] = fmaf(x.w, f, acc[e + 3]);
       }
     }
-    wait_vmcnt<0>();                         // this wave's loads of the next tile
-    __syncthreads();
-  }
-  if (q >= S) return;
-  // O^T[e][q] in o[t][r]: e = 32 t + 8 (r / 4) + 4 (l / 32) + r % 4
-  const float inv = 1.0f / l;
-  uint16_t* orow = O + (so + q) * d + hd * kHead;
+    const float inv = 1.0f / L;
+    float out[8];
 #pragma unroll
-  for (int t = 0; t < kHead / 32; ++t)
+    for (int e = 0; e < 16; e += 8) {
 #pragma unroll
-    for (int g4 = 0; g4 < 4; ++g4) {
-      const float v0 = o[t][4 * g4] * inv, v1 = o[t][4 * g4 + 1] * inv;
-      const float v2 = o[t][4 * g4 + 2] * inv, v3 = o[t][4 * g4 + 3] * inv;
-      uint2 w;
-      w.x = (uint32_t)f32_to_bf16(v0) | ((uint32_t)f32_to_bf16(v1) << 16);
-      w.y = (uint32_t)f32_to_bf16(v2) | ((uint32_t)f32_to_bf16(v3) << 16);
-      *reinterpret_cast<uint2*>(orow + 32 * t + 8 * g4 + 4 * half) = w;
+      for (int k = 0; k < 8; ++k) out[k] = acc[e + k] * inv;
+      store8(O + (so + qw + cq) * d + hd * kHead + e0 + e, out);
     }
+  } else {
+    if (q >= S) return;
+    const float inv = 1.0f / l;
+    uint16_t* orow = O + (so + q) * d + hd * kHead;
+#pragma unroll
+    for (int t = 0; t < kHead / 32; ++t)
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        bf16x4_t v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = (__bf16)(o[t][4 * g4 + r] * inv);
+        *reinterpret_cast<bf16x4_t*>(orow + 32 * t + 8 * g4 + 4 * half) = v;
+      }
+  }
+}
+
+// Attention takes kSplit while its workgroups (32 queries of a head; S rows in
+// the batch) fit one round of the 256 compute units, or one and a half when
+// causal, where the later ones have few keys.  us, kShared against kSplit, at
+// workgroups of kSplit: 160 17.9 / 11.5, 182 13.4 / 8.7, 264 19.2 / 22.7, 320
+// 17.9 / 20.4; causal: 276 26.9 / 17.4, 320 18.2 / 12.2, 384 16.7 / 15.6, 640
+// 18.9 / 22.5.  Counted from the batch's rows, so that neither the choice nor
+// the order of the sums depends on the max_seq that a caller passes.
+inline bool split_keys(int64_t S, int heads, bool causal) {
+  return S * heads <= (causal ? 384 : 256) * (int64_t)kQPerWave;
 }
 
 }  // namespace
-
-size_t encode_smax_pad(int max_seq) { return align_up((size_t)(max_seq > 0 ? max_seq : 1), kVtKeys); }
 
 hipError_t launch_encode(const EncodeArgs& a, hipStream_t stream) {
   if (a.T_vis == 0) return hipSuccess;             // no visual rows: nothing to output
   const int d = a.d;
   const int64_t S = a.T_vis + a.T_txt;
   const int heads = d / kHead;
-  const int smax_pad = (int)encode_smax_pad(a.max_seq);
   const unsigned row_blocks = (unsigned)((S + kRowWaves - 1) / kRowWaves);
   hipError_t e;
   // the sequences: visual rows, then the projected text rows
@@ -421,20 +520,19 @@ hipError_t launch_encode(const EncodeArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL(enc_ln_kernel, dim3(row_blocks), dim3(64 * kRowWaves), 0, stream, a.R, S, d,
                      a.blk[0].ln1_g, a.blk[0].ln1_b, a.L);
   const float c2 = 1.4426950408889634f / sqrtf((float)kHead);
-  const dim3 attn_grid((unsigned)((a.max_seq + kQPerWave * kAttnWaves - 1) / (kQPerWave * kAttnWaves)),
-                       (unsigned)heads, (unsigned)a.B);
-  const dim3 vt_grid((unsigned)(smax_pad / kVtKeys), (unsigned)heads, (unsigned)a.B);
+  const bool split = split_keys(S, heads, a.causal);
+  const int queries = split ? AttnShape<true>::QUERIES : AttnShape<false>::QUERIES;
+  const int q_blocks = (int)(((int64_t)a.max_seq + queries - 1) / queries);
+  auto* attn = split ? attn_kernel<true> : attn_kernel<false>;
+  const dim3 attn_grid((unsigned)((int64_t)q_blocks * heads), (unsigned)a.B);
   for (int k = 0; k < kEncoderBlocks; ++k) {
     const EncoderBlockArgs& p = a.blk[k];
     // q, k, v of LN1(R) (in L), biased in the product's epilogue
     if ((e = launch_dense_bf16(a.L, p.W_qkv, S, 3 * (int64_t)d, d, a.QKV, stream, p.b_qkv)) !=
         hipSuccess)
       return e;
-    hipLaunchKernelGGL(vt_kernel, vt_grid, dim3(256), 0, stream, a.QKV, d, smax_pad, a.img_off,
-                       a.text_off, a.max_seq, S, a.Vt, a.err);
-    hipLaunchKernelGGL(attn_kernel, attn_grid, dim3(64 * kAttnWaves), 0, stream, a.QKV, a.Vt, d,
-                       smax_pad, a.img_off, a.text_off, a.max_seq, S, a.causal ? 1 : 0, c2, a.A,
-                       a.err);
+    hipLaunchKernelGGL(attn, attn_grid, dim3(64 * kAttnWaves), 0, stream, a.QKV, d, q_blocks,
+                       a.img_off, a.text_off, a.max_seq, S, a.causal ? 1 : 0, c2, a.A, a.err);
     // R += A W_o^T + b_o; LN2 into A
     if ((e = launch_dense_bf16(a.A, p.W_o, S, d, d, a.L, stream)) != hipSuccess) return e;
     if ((e = launch_resid_ln(a.R, a.L, p.b_o, S, d, p.ln2_g, p.ln2_b, a.A, stream)) != hipSuccess)

@@ -195,7 +195,7 @@ hipError_t launch_resid_ln(float* xt, const uint16_t* t, const float* bias, int6
 // bfloat16 [out, in]; vectors float32.  Workspace buffers (rows of the
 // S = T_vis + T_txt sequence rows): R float32 [S, d] (the residual stream),
 // L and A bfloat16 [S, d], QKV bfloat16 [S, 3d], HID bfloat16 [S, 4d] (also the
-// text product [T_txt, d]), Vt bfloat16 [B, d, encode_smax_pad(max_seq)].
+// text product [T_txt, d]).
 constexpr int kEncoderBlocks = 2;
 struct EncoderBlockArgs {
   const float* ln1_g;
@@ -230,11 +230,8 @@ struct EncodeArgs {
   uint16_t* A;
   uint16_t* QKV;
   uint16_t* HID;
-  uint16_t* Vt;
   int32_t* err;
 };
-// Keys per image row of Vt: max_seq rounded up to the transpose tile.
-size_t encode_smax_pad(int max_seq);
 hipError_t launch_encode(const EncodeArgs& a, hipStream_t stream);
 
 }  // namespace sp
