@@ -8,10 +8,9 @@
 //    128 x 64 as 16 x 16 tiles of v_mfma_f32_16x16x32_bf16 (smaller tiles for
 //    small products and for the last round of a large one); K in 64-wide
 //    stages through LDS rings filled straight from global memory.
-//  * float32, gemm_block: BM x BN tiles of four waves, each owning a
-//    (BM/2) x (BN/2) quadrant of 32 x 32 tiles of v_mfma_f32_32x32x2_f32; K in
-//    BK-wide stages through two LDS buffers, the next stage fetched into
-//    registers while the current one feeds the matrix cores.
+//  * float32, gemm_f32: 32 x 64 or 64 x 64 tiles of four waves, as 16 x 16
+//    tiles of v_mfma_f32_16x16x4_f32; K in 64-wide stages through an LDS ring
+//    filled straight from global memory.
 //
 // Three users:
 //  * the projection of Algorithm 1 step 1: A = [X; s_start; s_stop], B = W_kqv;
@@ -30,7 +29,6 @@ namespace {
 
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
@@ -42,133 +40,120 @@ __device__ inline uint16_t f32_to_bf16_rne(float f) {
   return (uint16_t)(u >> 16);
 }
 
-template <typename OutT>
-__device__ inline OutT store_cvt(float v);
-template <>
-__device__ inline float store_cvt<float>(float v) { return v; }
-template <>
-__device__ inline uint16_t store_cvt<uint16_t>(float v) { return f32_to_bf16_rne(v); }
-
-// Geometry of the float32 core's tiles.
-template <typename T, int BM, int BN, int BK>
-struct Tile {
-  static_assert(sizeof(T) == 4, "the register-staged core is float32 only");
-  static constexpr int VEC = 16 / (int)sizeof(T);      // elements per 16-byte chunk
-  static constexpr int KM = 2;                          // K of one MFMA
-  static constexpr int LDK = BK + VEC;                  // padded LDS row, elements
-  static constexpr int CPR = BK / VEC;                  // chunks per tile row
-  static constexpr int CH_A = BM * CPR / kThreads;      // chunks per thread per stage
-  static constexpr int CH_B = BN * CPR / kThreads;
-  static constexpr int WM = BM / 2, WN = BN / 2;
-  static constexpr int TM = WM / 32, TN = WN / 32;
-  static constexpr int LDS_BYTES = 2 * (BM + BN) * LDK * (int)sizeof(T);
-  static_assert(BM * CPR % kThreads == 0 && BN * CPR % kThreads == 0, "tile/thread mismatch");
-  static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be a multiple of 32");
+// ------------------------------------------------------------------ float32
+//
+// One BM x 64 output tile of four waves (2 x 2, BM / 2 x 32 each), K in 64-wide
+// stages through a ring of D LDS buffers filled straight from global memory (a
+// 256-byte row is sixteen 16-byte chunks, chunk c of row r at slot c ^ (r & 15)),
+// D - 1 stages ahead of the matrix cores, one barrier a stage.
+//
+// What bounds it: with few tiles, a wave's own chain.  A 32 x 32 tile a wave in
+// v_mfma_f32_32x32x2_f32 (64 cycles for K = 2) takes 14 us for K = 1024 however
+// idle the chip is; 16 x 32 a wave halves that and doubles the workgroups.  With
+// many, the matrix cores (157 TFLOP/s).  A lane reads four consecutive k of its
+// row at a time and feeds them to four instructions, which then sum k = 4 (l /
+// 16) + i, i = 0..3: A and B agree on the order.  The product is formed
+// transposed (B as the row operand), so a lane holds four consecutive columns of
+// one row.
+// us against tiles of 64 x 64 or 128 x 128 staged through registers into 32-wide
+// stages, the text product in a launch of its own: projection and text of one
+// image, 578 x 768 x 1024, 46 -> 17; 1202 x 1536 x 1280 90 -> 53; 7202 x 1536 x
+// 1280 375 -> 272 (107 TFLOP/s); Gram products of 3 groups of 256 and less, h
+// 256, 10.8 -> 6.8, of 32, h 512, 74 -> 63.
+template <int BM_, int D_>
+struct F32Tile {
+  static constexpr int BM = BM_, BN = 64, KS = 64, D = D_, WAVES = 4;
+  static constexpr int TM = BM / 32;                               // 16-row tiles of a wave
+  static constexpr int ROW = KS * 4, BUF = (BM + BN) * ROW;        // a stage: 24 or 32 KB
+  static constexpr int LOADS = BUF / 1024 / WAVES;                 // per wave and stage
+  static constexpr int LDS = D * BUF;                              // two workgroups a CU
+  static_assert(BM % 32 == 0 && 2 * LDS <= kLdsBytes, "tile shape");
 };
+using F32Low = F32Tile<32, 3>;     // 72 KB
+using F32High = F32Tile<64, 2>;    // 64 KB
 
-// One BM x BN output tile.  ARows/BRows map a row index to its K-contiguous
-// storage; rows at or past M (N) read as zero and are not stored.
-template <typename T, typename OutT, int BM, int BN, int BK, class ARows, class BRows>
-__device__ __forceinline__ void gemm_block(const ARows& ar, const BRows& br, int64_t M, int64_t N,
-                                           int K, OutT* __restrict__ C, int64_t ldc, int64_t m0,
-                                           int64_t n0, char* smem) {
-  using G = Tile<T, BM, BN, BK>;
-  T* As = reinterpret_cast<T*>(smem);
-  T* Bs = As + 2 * BM * G::LDK;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-
-  const T* pa[G::CH_A];
-  const T* pb[G::CH_B];
-  int la[G::CH_A], lb[G::CH_B];
+template <class G, class ARows, class BRows>
+__device__ __forceinline__ void gemm_f32(const ARows& ar, const BRows& br, int64_t M, int64_t N,
+                                         int K, float* __restrict__ C, int64_t ldc, int64_t m0,
+                                         int64_t n0, char* smem) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, lk = lane >> 4;
+  // This wave loads 4-row groups wave + 4 q of the stage's A rows, then B rows;
+  // rows past M (N) read the last one and are not stored.
+  const int dchunk = l16 ^ ((4 * wave + lk) & 15);
+  const float* src[G::LOADS];
 #pragma unroll
-  for (int i = 0; i < G::CH_A; ++i) {
-    const int c = tid + i * kThreads;
-    const int row = c / G::CPR, kc = c % G::CPR;
-    const int64_t gm = m0 + row;
-    pa[i] = gm < M ? ar.row(gm) + kc * G::VEC : nullptr;
-    la[i] = row * G::LDK + kc * G::VEC;
-  }
-#pragma unroll
-  for (int i = 0; i < G::CH_B; ++i) {
-    const int c = tid + i * kThreads;
-    const int row = c / G::CPR, kc = c % G::CPR;
-    const int64_t gn = n0 + row;
-    pb[i] = gn < N ? br.row(gn) + kc * G::VEC : nullptr;
-    lb[i] = row * G::LDK + kc * G::VEC;
-  }
-
-  u32x4_t va[G::CH_A], vb[G::CH_B];
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < G::CH_A; ++i)
-      va[i] = pa[i] ? *reinterpret_cast<const u32x4_t*>(pa[i] + k0) : u32x4_t{0, 0, 0, 0};
-#pragma unroll
-    for (int i = 0; i < G::CH_B; ++i)
-      vb[i] = pb[i] ? *reinterpret_cast<const u32x4_t*>(pb[i] + k0) : u32x4_t{0, 0, 0, 0};
-  };
-  auto lstore = [&](int buf) {
-    T* a = As + buf * BM * G::LDK;
-    T* b = Bs + buf * BN * G::LDK;
-#pragma unroll
-    for (int i = 0; i < G::CH_A; ++i) *reinterpret_cast<u32x4_t*>(a + la[i]) = va[i];
-#pragma unroll
-    for (int i = 0; i < G::CH_B; ++i) *reinterpret_cast<u32x4_t*>(b + lb[i]) = vb[i];
-  };
-
-  f32x16_t acc[G::TM][G::TN];
-#pragma unroll
-  for (int i = 0; i < G::TM; ++i)
-#pragma unroll
-    for (int j = 0; j < G::TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-  const int KT = K / BK;
-  gload(0);
-  lstore(0);
-  __syncthreads();
-  const int arow = wm * G::WM + (lane & 31);
-  const int brow = wn * G::WN + (lane & 31);
-  for (int kt = 0; kt < KT; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < KT) gload((kt + 1) * BK);
-    const T* Ab = As + buf * BM * G::LDK;
-    const T* Bb = Bs + buf * BN * G::LDK;
-#pragma unroll
-    for (int ks = 0; ks < BK; ks += G::KM) {
-      float a[G::TM], b[G::TN];
-      const int koff = ks + (lane >> 5);
-#pragma unroll
-      for (int i = 0; i < G::TM; ++i) a[i] = Ab[(arow + i * 32) * G::LDK + koff];
-#pragma unroll
-      for (int j = 0; j < G::TN; ++j) b[j] = Bb[(brow + j * 32) * G::LDK + koff];
-#pragma unroll
-      for (int i = 0; i < G::TM; ++i)
-#pragma unroll
-        for (int j = 0; j < G::TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+  for (int q = 0; q < G::LOADS; ++q) {
+    const int r = 4 * (wave + G::WAVES * q) + lk;
+    if (4 * G::WAVES * q < G::BM) {
+      const int64_t gm = m0 + r;
+      src[q] = ar.row(gm < M ? gm : M - 1) + 4 * dchunk;
+    } else {
+      const int64_t gn = n0 + r - G::BM;
+      src[q] = br.row(gn < N ? gn : N - 1) + 4 * dchunk;
     }
-    if (kt + 1 < KT) lstore(buf ^ 1);
-    __syncthreads();
   }
-
-  // 32x32 MFMA result layout: lane l, register r holds
-  // row 8*(r/4) + 4*(l/32) + r%4, column l%32.
+  auto issue = [&](int kt, int slot) {
 #pragma unroll
-  for (int i = 0; i < G::TM; ++i)
+    for (int q = 0; q < G::LOADS; ++q)
+      lds_dma16(src[q] + kt * G::KS, smem + slot * G::BUF + (wave + G::WAVES * q) * 1024);
+  };
+  f32x4_t acc[G::TM][2];
 #pragma unroll
-    for (int j = 0; j < G::TN; ++j) {
-      const int64_t col = n0 + wn * G::WN + j * 32 + (lane & 31);
-      if (col >= N) continue;
+  for (int u = 0; u < G::TM; ++u) acc[u][0] = acc[u][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int arow = (wm * (G::BM / 2) + l16) * G::ROW, brow = (G::BM + wn * 32 + l16) * G::ROW;
+  const int KT = K / G::KS;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t row = m0 + wm * G::WM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (row < M) C[row * ldc + col] = store_cvt<OutT>(acc[i][j][r]);
+  for (int s = 0; s < G::D - 1; ++s)
+    if (s < KT) issue(s, s);
+  int slot = 0;
+  for (int kt = 0; kt < KT; ++kt) {
+    // stage kt has landed (only loads of later stages remain), and after the
+    // barrier every wave is past stage kt - 1, whose buffer is refilled
+    if (kt + G::D - 2 < KT) wait_vmcnt<(G::D - 2) * G::LOADS>();
+    else wait_vmcnt<0>();
+    wait_lgkm0();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (kt + G::D - 1 < KT) issue(kt + G::D - 1, slot == 0 ? G::D - 1 : slot - 1);
+    const char* st = smem + slot * G::BUF;
+#pragma unroll
+    for (int c = 0; c < G::KS / 16; ++c) {
+      const int ch = ((4 * c + lk) ^ l16) << 4;
+      f32x4_t a[G::TM];
+#pragma unroll
+      for (int u = 0; u < G::TM; ++u)
+        a[u] = *reinterpret_cast<const f32x4_t*>(st + arow + u * 16 * G::ROW + ch);
+      const f32x4_t b0 = *reinterpret_cast<const f32x4_t*>(st + brow + ch);
+      const f32x4_t b1 = *reinterpret_cast<const f32x4_t*>(st + brow + 16 * G::ROW + ch);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int u = 0; u < G::TM; ++u) {
+          acc[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(b0[i], a[u][i], acc[u][0], 0, 0, 0);
+          acc[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(b1[i], a[u][i], acc[u][1], 0, 0, 0);
+        }
+    }
+    slot = slot == G::D - 1 ? 0 : slot + 1;
+  }
+  // lane l, register r: row l % 16, column 4 (l / 16) + r of a 16 x 16 tile
+#pragma unroll
+  for (int u = 0; u < G::TM; ++u) {
+    const int64_t row = m0 + wm * (G::BM / 2) + 16 * u + l16;
+    if (row >= M) continue;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int64_t col = n0 + wn * 32 + 16 * t + 4 * lk;
+      float* dst = C + row * ldc + col;              // 16-byte aligned: C, ldc and col are
+      if (col + 4 <= N) {
+        *reinterpret_cast<f32x4_t*>(dst) = acc[u][t];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (col + e < N) dst[e] = acc[u][t][e];
       }
     }
+  }
 }
 
 // ------------------------------------------------------------------ bf16
@@ -789,14 +774,41 @@ struct GramStrips {
 
 // ------------------------------------------------------------------ kernels
 
-template <typename T, typename OutT, int BM, int BN, int BK>
-__global__ __launch_bounds__(kThreads) void project_gemm_kernel(ProjRows<T> ar, DenseRows<T> br,
-                                                                int64_t M, int64_t N, int K,
-                                                                OutT* C) {
-  __shared__ __attribute__((aligned(16))) char smem[Tile<T, BM, BN, BK>::LDS_BYTES];
-  const int64_t nt = (N + BN - 1) / BN;
-  const int64_t t = blockIdx.x;
-  gemm_block<T, OutT, BM, BN, BK>(ar, br, M, N, K, C, N, (t / nt) * BM, (t % nt) * BN, smem);
+// float32: the projection's tiles, then the text projection's, split over K into
+// partial products of K2 each (part p of the product at C2 + p M2 N2).  Tiles in
+// row-major order: workgroup w runs on XCD w % 8, so where the column panels are a
+// multiple of four, an XCD reads a half to an eighth of the weights.  With a
+// contiguous run of tiles an XCD instead, 578 x 768 x 1024 took 25 us, not 16.
+struct ProjectF32Args {
+  ProjRows<float> ar;
+  DenseRows<float> br;
+  int64_t M, N, tiles;
+  int K;
+  float* C;
+  DenseRows<float> er, wr;
+  int64_t M2, N2, tiles2;       // tiles of one part
+  int K2, split;
+  float* C2;
+};
+
+template <class G>
+__global__ __launch_bounds__(kThreads) void project_gemm_f32_kernel(ProjectF32Args p) {
+  __shared__ __attribute__((aligned(1024))) char smem[G::LDS];
+  int64_t t = blockIdx.x;
+  if (t < p.tiles) {
+    const int64_t nt = (p.N + G::BN - 1) / G::BN;
+    gemm_f32<G>(p.ar, p.br, p.M, p.N, p.K, p.C, p.N, (t / nt) * G::BM, (t % nt) * G::BN, smem);
+  } else {
+    t -= p.tiles;
+    const int64_t nt = (p.N2 + G::BN - 1) / G::BN, part = t / p.tiles2, i = t % p.tiles2;
+    DenseRows<float> a, b;
+    a.base = p.er.base + part * p.K2;
+    a.ld = p.er.ld;
+    b.base = p.wr.base + part * p.K2;
+    b.ld = p.wr.ld;
+    gemm_f32<G>(a, b, p.M2, p.N2, p.K2, p.C2 + part * p.M2 * p.N2, p.N2, (i / nt) * G::BM,
+                (i % nt) * G::BN, smem);
+  }
 }
 
 constexpr int kBfThreads = TileWhole::THREADS;
@@ -919,21 +931,6 @@ __global__ __launch_bounds__(TileSmall::THREADS) void dense_bf16_small_kernel(
   gemm_bf16<TileSmall, uint16_t, Rows, Rows, EPI>(ar, br, M, N, K, C, N, m0, n0, smem, bias);
 }
 
-// grid.x: output tiles, grid.y: K split p, which covers k in [p K, (p + 1) K)
-// and writes partial product p at C + p M N.
-template <typename T, int BM, int BN, int BK>
-__global__ __launch_bounds__(kThreads) void dense_gemm_kernel(DenseRows<T> ar, DenseRows<T> br,
-                                                              int64_t M, int64_t N, int K,
-                                                              float* C) {
-  __shared__ __attribute__((aligned(16))) char smem[Tile<T, BM, BN, BK>::LDS_BYTES];
-  const int64_t nt = (N + BN - 1) / BN;
-  const int64_t t = blockIdx.x;
-  const int64_t k0 = (int64_t)blockIdx.y * K;
-  DenseRows<T> a{ar.base + k0, ar.ld}, b{br.base + k0, br.ld};
-  gemm_block<T, float, BM, BN, BK>(a, b, M, N, K, C + blockIdx.y * M * N, N, (t / nt) * BM,
-                                   (t % nt) * BN, smem);
-}
-
 // The context of image b as three rows of the working dtype whose sum is the
 // float32 value exactly (bfloat16: successive round-to-nearest-even residuals,
 // 3 x 8 significant bits; float32: the value and two zero rows).
@@ -1050,12 +1047,10 @@ __global__ __launch_bounds__(kBfThreads) void gram_gemm_bf16_kernel(GramArgs a, 
   }
 }
 
-// float32 Gram products on the register-staged core, BM x BN tiles.
-template <int BM, int BN>
-__global__ __launch_bounds__(kThreads) void gram_gemm_f32_kernel(GramArgs a, int per_group,
-                                                                int xcd_grouped) {
-  constexpr int BK = 32;
-  __shared__ __attribute__((aligned(16))) char smem[Tile<float, BM, BN, BK>::LDS_BYTES];
+// float32 Gram products, all rows and columns in the tiles.
+template <class G>
+__global__ __launch_bounds__(kThreads) void gram_gemm_f32_kernel(GramArgs a, int per_group, int xcd_grouped) {
+  __shared__ __attribute__((aligned(1024))) char smem[G::LDS];
   int64_t g, t, g0, n;
   int b;
   if (!gram_tile(blockIdx.x, per_group, a.G, xcd_grouped, g, t)) return;
@@ -1063,22 +1058,25 @@ __global__ __launch_bounds__(kThreads) void gram_gemm_f32_kernel(GramArgs a, int
   const float* KQV = static_cast<const float*>(a.KQV);
   const float* cs = static_cast<const float*>(a.csplit) + (int64_t)b * kGramExtraRows * a.h;
   const int64_t M = 2 * (n + 1) + kGramExtraRows, N = n + 2;
-  const int64_t nt = (a.max_group + 2 + BN - 1) / BN;
-  const int64_t m0 = (t / nt) * BM, n0 = (t % nt) * BN;
+  const int64_t nt = (a.max_group + 2 + G::BN - 1) / G::BN;
+  const int64_t m0 = (t / nt) * G::BM, n0 = (t % nt) * G::BN;
   if (m0 >= M || n0 >= N) return;
   GramARows<float> ar{KQV, g0, n, a.T_vis, a.h, cs};
   GramBRows<float> br{KQV, g0, n, a.T_vis, a.h};
-  gemm_block<float, float, BM, BN, BK>(ar, br, M, N, a.h, a.gram + g * a.gram_group_stride,
-                                       a.gram_ld, m0, n0, smem);
+  gemm_f32<G>(ar, br, M, N, a.h, a.gram + g * a.gram_group_stride, a.gram_ld, m0, n0, smem);
 }
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// The float32 paths serve small batches (one image of a few hundred tokens):
-// 128 x 128 tiles would leave most compute units idle, so 64 x 64 tiles are
-// taken while the 128 x 128 ones would not fill the chip once.  Each output
-// accumulates its K in the same order either way.
-inline bool small_f32_tiles(int64_t M, int64_t N) { return ceil_div(M, 128) * ceil_div(N, 128) < 256; }
+template <class G>
+inline int64_t f32_tiles(int64_t M, int64_t N) { return ceil_div(M, G::BM) * ceil_div(N, G::BN); }
+
+// 32 x 64 tiles while 64 x 64 ones would be at most 400, less than a round of
+// 512 (two a compute unit).  us, 32 x 64 against 64 x 64 tiles (projection with
+// text), at 64 x 64 tiles: 120 17.6 / 24.4, 228 35.3 / 35.6, 384 59.0 / 62.0,
+// 456 60.2 / 53.4, 918 113 / 100, 2712 304 / 272.  Every element accumulates K in
+// the same order either way.
+inline bool f32_low(int64_t M, int64_t N) { return f32_tiles<F32High>(M, N) <= 400; }
 
 }  // namespace
 
@@ -1091,23 +1089,6 @@ int text_split(int dtype, int64_t T_txt, int h, int d_text) {
   while (s < 8 && tiles * s < 512 && d_text % (2 * s * 64) == 0) s *= 2;
   return s;
 }
-
-namespace {
-
-hipError_t launch_text_gemm_f32(const void* E, int64_t T_txt, const void* W, int d_text, int h,
-                                float* out, hipStream_t stream) {
-  if (T_txt == 0) return hipSuccess;
-  const int split = text_split(SP_F32, T_txt, h, d_text);
-  const int kpart = d_text / split;
-  const dim3 grid((unsigned)(ceil_div(T_txt, 128) * ceil_div(h, 128)), (unsigned)split);
-  DenseRows<float> ar{(const float*)E, d_text};
-  DenseRows<float> br{(const float*)W, d_text};
-  hipLaunchKernelGGL((dense_gemm_kernel<float, 128, 128, 32>), grid, dim3(kThreads), 0, stream,
-                     ar, br, T_txt, (int64_t)h, kpart, out);
-  return hipGetLastError();
-}
-
-}  // namespace
 
 hipError_t launch_project_gemm(int dtype, const void* X, int64_t T_vis, const void* s_start,
                                const void* s_stop, const void* W, int d, int n_out, void* out,
@@ -1136,19 +1117,20 @@ hipError_t launch_project_gemm(int dtype, const void* X, int64_t T_vis, const vo
                          stream, args(DenseRows<__bf16>{}));
     return hipGetLastError();
   }
-  ProjRows<float> ar{{}, (const float*)X, T_vis, (const float*)s_start, (const float*)s_stop, d};
-  DenseRows<float> br{(const float*)W, d};
-  if (small_f32_tiles(M, N))
-    hipLaunchKernelGGL((project_gemm_kernel<float, float, 64, 64, 32>),
-                       dim3((unsigned)(ceil_div(M, 64) * ceil_div(N, 64))), dim3(kThreads), 0, stream,
-                       ar, br, M, N, d, (float*)out);
-  else
-    hipLaunchKernelGGL((project_gemm_kernel<float, float, 128, 128, 32>),
-                       dim3((unsigned)(ceil_div(M, 128) * ceil_div(N, 128))), dim3(kThreads), 0,
-                       stream, ar, br, M, N, d, (float*)out);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_text_gemm_f32(E, T_txt, W_text, d_text, h, tproj, stream);
+  auto launch = [&](auto tile) {
+    using G = decltype(tile);
+    const int split = text_split(SP_F32, T_txt, h, d_text);
+    const int64_t tiles = f32_tiles<G>(M, N), tiles2 = f32_tiles<G>(T_txt, h);
+    const ProjectF32Args p{ProjRows<float>{{}, (const float*)X, T_vis, (const float*)s_start, (const float*)s_stop, d},
+                           DenseRows<float>{(const float*)W, d}, M, N, tiles, d, (float*)out,
+                           DenseRows<float>{(const float*)E, d_text}, DenseRows<float>{(const float*)W_text, d_text},
+                           T_txt, (int64_t)h, tiles2, d_text / split, split, tproj};
+    hipLaunchKernelGGL(project_gemm_f32_kernel<G>, dim3((unsigned)(tiles + tiles2 * split)),
+                       dim3(kThreads), 0, stream, p);
+  };
+  if (f32_low(M, N)) launch(F32Low{});
+  else launch(F32High{});
+  return hipGetLastError();
 }
 
 namespace {
@@ -1189,17 +1171,15 @@ hipError_t launch_gram_gemm(const GramArgs& a, hipStream_t stream) {
   } else {
     hipLaunchKernelGGL(ctx_split_kernel<float>, dim3(a.B), dim3(256), 0, stream, a.ctx, a.h,
                        (float*)a.csplit);
-    const bool small = small_f32_tiles(M * a.G, N);
-    const int T = small ? 64 : 128;
-    const int per_group = (int)(ceil_div(M, T) * ceil_div(N, T));
-    const int64_t blocks =
-        xcd_grouped ? 8 * ceil_div(a.G, 8) * per_group : (int64_t)a.G * per_group;
-    if (small)
-      hipLaunchKernelGGL((gram_gemm_f32_kernel<64, 64>), dim3((unsigned)blocks), dim3(kThreads), 0,
-                         stream, a, per_group, xcd_grouped);
-    else
-      hipLaunchKernelGGL((gram_gemm_f32_kernel<128, 128>), dim3((unsigned)blocks), dim3(kThreads), 0,
-                         stream, a, per_group, xcd_grouped);
+    auto launch = [&](auto tile) {
+      using G = decltype(tile);
+      const int per_group = (int)f32_tiles<G>(M, N);
+      const int64_t blocks = xcd_grouped ? 8 * ceil_div(a.G, 8) * per_group : (int64_t)a.G * per_group;
+      hipLaunchKernelGGL(gram_gemm_f32_kernel<G>, dim3((unsigned)blocks), dim3(kThreads), 0, stream, a,
+                         per_group, xcd_grouped);
+    };
+    if (f32_low(M * a.G, N)) launch(F32Low{});
+    else launch(F32High{});
   }
   return hipGetLastError();
 }

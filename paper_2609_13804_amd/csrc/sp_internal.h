@@ -40,10 +40,9 @@ __device__ inline void set_device_error(int32_t* err, int32_t code) {
 // Projection: A rows are X rows 0..T_vis-1, then s_start, then s_stop; and
 // the text projection: A = E_text [T_txt, d_text], B = W_text [h, d_text],
 // float32 output split over K into text_split() partial products
-// [split][T_txt][h], which launch_text_pool adds in a fixed order.  For
-// bfloat16 both products run in one launch (the text tiles fill the compute
-// units the projection's last round leaves idle) and the text product is not
-// split.
+// [split][T_txt][h], which launch_text_pool adds in a fixed order.  Both
+// products run in one launch (the text tiles fill the compute units that the
+// projection's last round leaves idle); the bfloat16 text product is not split.
 int text_split(int dtype, int64_t T_txt, int h, int d_text);
 hipError_t launch_project_gemm(int dtype, const void* X, int64_t T_vis, const void* s_start,
                                const void* s_stop, const void* W, int d, int n_out, void* out,
