@@ -72,87 +72,69 @@ __device__ __forceinline__ bool sequence_of(const int32_t* __restrict__ img_off,
 
 // ---------------------------------------------------------------- row kernels
 
-// R[i + text_off[b]] = X[i], one workgroup per visual row.
-__global__ __launch_bounds__(256) void enc_visual_kernel(
-    const uint16_t* __restrict__ X, int d, const int32_t* __restrict__ img_off,
-    const int32_t* __restrict__ text_off, int B, int64_t S_total, float* __restrict__ R,
-    int32_t* err) {
-  const int64_t i = blockIdx.x;
-  const int b = owner(img_off, B, i);
-  const int64_t s = i + text_off[b];
-  if (s < 0 || s >= S_total) {
-    if (threadIdx.x == 0) set_device_error(err, SP_DEV_BAD_OFFSETS);
-    return;
-  }
-  for (int c = 8 * threadIdx.x; c < d; c += 8 * 256) {
-    float v[8];
-    load8(X + i * d + c, v);
-    store8(R + s * d + c, v);
-  }
-}
-
-// R[img_off[b + 1] + t] = g LN(P[t]) for text row t (LayerNorm without scale
-// or shift, biased variance, eps 1e-5).  One wave per row.
-__global__ __launch_bounds__(64 * kRowWaves) void enc_text_kernel(
-    const uint16_t* __restrict__ P, int64_t T_txt, int d, const int32_t* __restrict__ img_off,
-    const int32_t* __restrict__ text_off, int B, int64_t S_total, float g, float* __restrict__ R,
-    int32_t* err) {
+// Sequence row s: R = its visual row of X, or g LN(P) of its text row (LayerNorm
+// without scale or shift, biased variance, eps 1e-5), and Z = LN1(R) of the first
+// block.  One wave per row.  Bound by memory: R is written and not read back.
+// Against a kernel for the text rows, one for the visual rows and one for LN1, a
+// pass on one image of 1077 rows at width 1024 210 -> 207 us.
+__global__ __launch_bounds__(64 * kRowWaves) void enc_input_kernel(
+    const uint16_t* __restrict__ X, int64_t T_vis, const uint16_t* __restrict__ P, int64_t T_txt, int d,
+    const int32_t* __restrict__ img_off, const int32_t* __restrict__ text_off, int B, float g,
+    const float* __restrict__ ln_g, const float* __restrict__ ln_b, float* __restrict__ R,
+    uint16_t* __restrict__ Z, int32_t* err) {
   const int lane = threadIdx.x & 63;
-  const int64_t t = (int64_t)blockIdx.x * kRowWaves + (threadIdx.x >> 6);
-  if (t >= T_txt) return;
-  const int b = owner(text_off, B, t);
-  const int64_t s = (int64_t)img_off[b + 1] + t;
-  if (s < 0 || s >= S_total) {
+  const int64_t s = (int64_t)blockIdx.x * kRowWaves + (threadIdx.x >> 6);
+  if (s >= T_vis + T_txt) return;
+  int b = 0;                                  // the last image whose sequence starts at or before s
+  for (int hi = B; hi - b > 1;) {
+    const int mid = (b + hi) >> 1;
+    if ((int64_t)img_off[mid] + text_off[mid] <= s) b = mid;
+    else hi = mid;
+  }
+  const int64_t i = s - text_off[b], t = s - img_off[b + 1];      // as a visual row, as a text row
+  const bool text = i >= img_off[b + 1];
+  if (i < img_off[b] || t >= text_off[b + 1]) return;             // no image's row
+  if (text ? t < 0 || t >= T_txt : i < 0 || i >= T_vis) {
     if (lane == 0) set_device_error(err, SP_DEV_BAD_OFFSETS);
     return;
   }
-  const int nch = d / 8;
-  float v[kMaxChunks][8];
-  float sum = 0.0f;
-#pragma unroll
-  for (int i = 0; i < kMaxChunks; ++i) {
-    if (lane + 64 * i >= nch) break;
-    load8(P + t * d + 8 * (lane + 64 * i), v[i]);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) sum += v[i][k];
-  }
-  const float mean = wave_sum(sum) / (float)d;
-  float q = 0.0f;
-#pragma unroll
-  for (int i = 0; i < kMaxChunks; ++i) {
-    if (lane + 64 * i >= nch) break;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const float u = v[i][k] - mean;
-      q = fmaf(u, u, q);
-    }
-  }
-  const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)d + kTextLnEps);
-#pragma unroll
-  for (int i = 0; i < kMaxChunks; ++i) {
-    if (lane + 64 * i >= nch) break;
-    float o[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) o[k] = g * ((v[i][k] - mean) * rstd);
-    store8(R + s * d + 8 * (lane + 64 * i), o);
-  }
-}
-
-// Z = LN(R) with scale g and shift b (the first block's LN1).  One wave per row.
-__global__ __launch_bounds__(64 * kRowWaves) void enc_ln_kernel(
-    const float* __restrict__ R, int64_t S, int d, const float* __restrict__ g,
-    const float* __restrict__ b, uint16_t* __restrict__ Z) {
-  const int lane = threadIdx.x & 63;
-  const int64_t r = (int64_t)blockIdx.x * kRowWaves + (threadIdx.x >> 6);
-  if (r >= S) return;
+  const uint16_t* src = text ? P + t * d : X + i * d;
   const int nch = d / 8;
   float v[kMaxChunks][8];
 #pragma unroll
-  for (int i = 0; i < kMaxChunks; ++i) {
-    if (lane + 64 * i >= nch) break;
-    load8(R + r * d + 8 * (lane + 64 * i), v[i]);
+  for (int c = 0; c < kMaxChunks; ++c) {
+    if (lane + 64 * c >= nch) break;
+    load8(src + 8 * (lane + 64 * c), v[c]);
   }
-  ln_store(v, nch, d, lane, g, b, Z + r * d);
+  if (text) {
+    float sum = 0.0f;
+#pragma unroll
+    for (int c = 0; c < kMaxChunks; ++c)
+      if (lane + 64 * c < nch)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) sum += v[c][k];
+    const float mean = wave_sum(sum) / (float)d;
+    float q = 0.0f;
+#pragma unroll
+    for (int c = 0; c < kMaxChunks; ++c)
+      if (lane + 64 * c < nch)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const float u = v[c][k] - mean;
+          q = fmaf(u, u, q);
+        }
+    const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)d + kTextLnEps);
+#pragma unroll
+    for (int c = 0; c < kMaxChunks; ++c)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[c][k] = g * ((v[c][k] - mean) * rstd);
+  }
+#pragma unroll
+  for (int c = 0; c < kMaxChunks; ++c) {
+    if (lane + 64 * c >= nch) break;
+    store8(R + s * d + 8 * (lane + 64 * c), v[c]);
+  }
+  ln_store(v, nch, d, lane, ln_g, ln_b, Z + s * d);
 }
 
 // H[i] = bf16((R[s] + T[s]) + bias) for visual row i (s = i + text_off[b]):
@@ -511,14 +493,10 @@ hipError_t launch_encode(const EncodeArgs& a, hipStream_t stream) {
   if (a.T_txt > 0) {
     if ((e = launch_dense_bf16(a.E, a.W_p, a.T_txt, d, a.d_text, a.HID, stream)) != hipSuccess)
       return e;
-    hipLaunchKernelGGL(enc_text_kernel, dim3((unsigned)((a.T_txt + kRowWaves - 1) / kRowWaves)),
-                       dim3(64 * kRowWaves), 0, stream, a.HID, a.T_txt, d, a.img_off, a.text_off,
-                       a.B, S, a.g_text, a.R, a.err);
   }
-  hipLaunchKernelGGL(enc_visual_kernel, dim3((unsigned)a.T_vis), dim3(256), 0, stream, a.X, d,
-                     a.img_off, a.text_off, a.B, S, a.R, a.err);
-  hipLaunchKernelGGL(enc_ln_kernel, dim3(row_blocks), dim3(64 * kRowWaves), 0, stream, a.R, S, d,
-                     a.blk[0].ln1_g, a.blk[0].ln1_b, a.L);
+  hipLaunchKernelGGL(enc_input_kernel, dim3(row_blocks), dim3(64 * kRowWaves), 0, stream, a.X, a.T_vis,
+                     a.HID, a.T_txt, d, a.img_off, a.text_off, a.B, a.g_text, a.blk[0].ln1_g,
+                     a.blk[0].ln1_b, a.R, a.L, a.err);
   const float c2 = 1.4426950408889634f / sqrtf((float)kHead);
   const bool split = split_keys(S, heads, a.causal);
   const int queries = split ? AttnShape<true>::QUERIES : AttnShape<false>::QUERIES;
