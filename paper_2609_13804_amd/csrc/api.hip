@@ -37,22 +37,20 @@ sp_status check_dims(const sp_dims* d) {
 int elem_bytes(const sp_dims* d) { return d->dtype == SP_F32 ? 4 : 2; }
 
 struct SelectWs {
-  size_t gram, csplit, kept, count, total;
+  size_t gram, kept, count, total;
   int64_t gstride;
   int gram_ld;
 };
 
-// Header; Gram blocks [G][2 (max_group + 1) + 3][ld] float32; context split
-// [B][3][h] in the working dtype; group-local kept lists; group counts.
-SelectWs select_ws_layout(const sp_dims* d, int B, int G, int max_group, int max_cap) {
+// Header; Gram blocks [G][2 (max_group + 1) + 3][ld] float32; group-local kept
+// lists; group counts.
+SelectWs select_ws_layout(int G, int max_group, int max_cap) {
   SelectWs w;
   w.gram_ld = (int)align_up((size_t)max_group + 2, 4);
   w.gstride = (int64_t)(2 * (max_group + 1) + kGramExtraRows) * w.gram_ld;
   size_t off = kWsHeaderBytes;
   w.gram = off;
   off = align_up(off + (size_t)G * w.gstride * 4, 256);
-  w.csplit = off;
-  off = align_up(off + (size_t)B * kGramExtraRows * d->h * elem_bytes(d), 256);
   w.kept = off;
   off = align_up(off + (size_t)G * (max_cap > 0 ? max_cap : 1) * 4, 256);
   w.count = off;
@@ -138,7 +136,7 @@ size_t stepprune_workspace_bytes(int32_t which, const sp_dims* dims, int64_t T_v
     case 0: return project_ws_bytes(dims, T_txt);
     case 1:
       if (max_group < 0 || max_group > kMaxGroup || max_cap < 0) return 0;
-      return select_ws_layout(dims, B, G, max_group, max_cap).total;
+      return select_ws_layout(G, max_group, max_cap).total;
     case 2: return kWsHeaderBytes;
     case 3:
       if (dims->dtype != SP_BF16 || dims->d > 4096) return 0;
@@ -256,7 +254,7 @@ sp_status select_impl(const sp_dims* dims, const void* KQV, const float* ctx, in
     if (g != 1) return SP_EUNSUPPORTED;
   }
   if (!aligned16(KQV) || !aligned16(ctx) || (!use_scratch && !aligned16(ws))) return SP_EINVAL;
-  const SelectWs lay = select_ws_layout(dims, B, G, max_group, max_cap);
+  const SelectWs lay = select_ws_layout(G, max_group, max_cap);
   if (use_scratch) {
     if (lay.total > (size_t)STEPPRUNE_NOALLOC_SCRATCH_BYTES) return SP_EWORKSPACE;
     const sp_status sst = device_scratch(stream, &ws);
@@ -298,7 +296,6 @@ sp_status select_impl(const sp_dims* dims, const void* KQV, const float* ctx, in
   a.gram = reinterpret_cast<float*>(wsb + lay.gram);
   a.gram_group_stride = lay.gstride;
   a.gram_ld = lay.gram_ld;
-  a.csplit = wsb + lay.csplit;
   a.grp_kept = reinterpret_cast<int32_t*>(wsb + lay.kept);
   a.grp_count = reinterpret_cast<int32_t*>(wsb + lay.count);
   a.err = use_scratch ? err_word : reinterpret_cast<int32_t*>(wsb);

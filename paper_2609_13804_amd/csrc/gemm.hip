@@ -34,12 +34,6 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
 
-__device__ inline uint16_t f32_to_bf16_rne(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
 // ------------------------------------------------------------------ float32
 //
 // One BM x 64 output tile of four waves (2 x 2, BM / 2 x 32 each), K in 64-wide
@@ -313,6 +307,8 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
   // buffer just freed), a few at a time between the matrix instructions.
   const int KT = K / kKStage;
   if constexpr (SC || SR) strips.load(K, smem + G::LDS);   // the oldest loads: any wait below covers them
+  [[maybe_unused]] f32x4_t cx;
+  if constexpr (SR) strips.ctx_load(K, cx);
 #pragma unroll
   for (int s = 0; s < D; ++s)
     if (s < KT) {
@@ -321,8 +317,10 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
 #pragma unroll
       for (int q = 0; q < LB; ++q) issue_b(s, q, s);
     }
+  if constexpr (SR) strips.ctx_store(K, cx, smem + G::LDS);
   if (KT >= D) wait_vmcnt<(D - 1) * (LA + LB)>();
   else wait_vmcnt<0>();
+  if constexpr (SR) wait_lgkm0();          // ctx_store's writes
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 #pragma unroll
@@ -661,21 +659,22 @@ struct WideRows : AnyRows<WideRows> {
 };
 
 // float32 Gram operand rows of one group with tokens [g0, g0 + n): A side is
-// [Q tokens; q_start; V tokens; v_start; c_hi; c_mid; c_lo] (the last three
-// from the image's context split), B side is [K tokens; k_stop; k_start].
+// [Q tokens; q_start; V tokens; v_start; c; 0; 0], B side is [K tokens; k_stop;
+// k_start].
+__device__ const float zero_row[512] = {};     // sp_dims' limit on a float32 h
 template <typename T>
 struct GramARows {
   const T* KQV;
   int64_t g0, n, start_row;
   int h;
-  const T* csplit;     // the image's three context rows
+  const T* ctx;        // the image's context
   __device__ const T* row(int64_t r) const {
     const int64_t ld = 3 * (int64_t)h;
     if (r < n) return KQV + (g0 + r) * ld + h;
     if (r == n) return KQV + start_row * ld + h;
     if (r < 2 * n + 1) return KQV + (g0 + r - n - 1) * ld + 2 * h;
     if (r == 2 * n + 1) return KQV + start_row * ld + 2 * h;
-    return csplit + (r - 2 * n - 2) * h;
+    return r == 2 * n + 2 ? ctx : zero_row;
   }
 };
 
@@ -719,24 +718,51 @@ struct GramTokenBRows : AnyRows<GramTokenBRows> {
 // [k_stop; k_start] (kCols) of a group's Gram block.  Their seven operand rows
 // are loaded into LDS whole, row stride 2 h + 16 bytes (the five rows a
 // fragment read touches fall on different banks); a fragment's lanes past them
-// repeat a row and are not stored.
+// repeat a row and are not stored.  The last three rows are the image's float32
+// context as bfloat16 values whose sum it is exactly (successive
+// round-to-nearest-even residuals, 3 x 8 significant bits); four waves split it on
+// the way, while the first stages load: a launch that wrote the split to memory
+// before cost 3 to 4 us a selection.
 template <bool COLS, bool ROWS>
 struct GramStrips {
   static constexpr bool kCols = COLS, kRows = ROWS;
   static constexpr int kMaxH = 1024;                       // sp_dims' limit
   static constexpr int LDS = 7 * (2 * kMaxH + 16);
   const __bf16* start;      // START's projected row [k | q | v], STOP's after it
-  const __bf16* csplit;     // the image's three context rows
+  const float* ctx;         // the image's context
   int64_t n;
   int h;
   __device__ int stride() const { return 2 * h + 16; }
   __device__ void load(int K, char* dst) const {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (w >= 7) return;
-    const __bf16* row = w == 0 ? start + h : w == 1 ? start + 2 * h : w < 5 ? csplit + (w - 2) * h
-                      : w == 5 ? start + 3 * h : start;
+    if (w == 7 || (w >= 2 && w < 5)) return;
+    const __bf16* row = w == 0 ? start + h : w == 1 ? start + 2 * h : w == 5 ? start + 3 * h : start;
     for (int c = 0; c < K; c += 512)
       if (c + 8 * lane < K) lds_dma16(row + c + 8 * lane, dst + w * stride() + 2 * c);
+  }
+  // The other four waves' part: 256 values of the context each, four a lane, then
+  // their three rows.
+  __device__ int ctx_at() const {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    return w == 7 || (w >= 2 && w < 5) ? 256 * (w == 7 ? 3 : w - 2) + 4 * (int)(threadIdx.x & 63) : kMaxH;
+  }
+  __device__ void ctx_load(int K, f32x4_t& v) const {
+    const int c = ctx_at();
+    if (c < K) v = *reinterpret_cast<const f32x4_t*>(ctx + c);
+  }
+  __device__ void ctx_store(int K, f32x4_t v, char* dst) const {
+    const int c = ctx_at();
+    if (c >= K) return;
+#pragma unroll
+    for (int part = 0; part < 3; ++part) {
+      bf16x4_t x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[e] = (__bf16)v[e];
+        v[e] -= (float)x[e];
+      }
+      *reinterpret_cast<bf16x4_t*>(dst + (2 + part) * stride() + 2 * c) = x;
+    }
   }
   __device__ bf16x8_t at(const char* s, int r, int k) const {
     return *reinterpret_cast<const bf16x8_t*>(s + r * stride() + 2 * k);
@@ -931,33 +957,6 @@ __global__ __launch_bounds__(TileSmall::THREADS) void dense_bf16_small_kernel(
   gemm_bf16<TileSmall, uint16_t, Rows, Rows, EPI>(ar, br, M, N, K, C, N, m0, n0, smem, bias);
 }
 
-// The context of image b as three rows of the working dtype whose sum is the
-// float32 value exactly (bfloat16: successive round-to-nearest-even residuals,
-// 3 x 8 significant bits; float32: the value and two zero rows).
-template <typename T>
-__global__ __launch_bounds__(256) void ctx_split_kernel(const float* __restrict__ ctx, int h,
-                                                        T* __restrict__ csplit) {
-  const int b = blockIdx.x;
-  for (int i = threadIdx.x; i < h; i += blockDim.x) {
-    const float c = ctx[(int64_t)b * h + i];
-    T* out = csplit + (int64_t)b * kGramExtraRows * h + i;
-    if constexpr (sizeof(T) == 2) {
-      const uint16_t hi = f32_to_bf16_rne(c);
-      const float r1 = c - __uint_as_float((uint32_t)hi << 16);
-      const uint16_t mid = f32_to_bf16_rne(r1);
-      const float r2 = r1 - __uint_as_float((uint32_t)mid << 16);
-      const uint16_t lo = f32_to_bf16_rne(r2);
-      reinterpret_cast<uint16_t*>(out)[0] = hi;
-      reinterpret_cast<uint16_t*>(out)[h] = mid;
-      reinterpret_cast<uint16_t*>(out)[2 * h] = lo;
-    } else {
-      out[0] = c;
-      out[h] = 0.0f;
-      out[2 * h] = 0.0f;
-    }
-  }
-}
-
 // Workgroup w runs on XCD w % 8.  With at least eight groups, all tiles of a
 // group are placed on one XCD (group x + 8 k on XCD x) so that the group's
 // rows are fetched into one L2.
@@ -1029,12 +1028,12 @@ __global__ __launch_bounds__(kBfThreads) void gram_gemm_bf16_kernel(GramArgs a, 
   br.start_row = a.T_vis;
   br.h = a.h;
   const __bf16* start = KQV + a.T_vis * 3 * (int64_t)a.h;
-  const __bf16* cs = static_cast<const __bf16*>(a.csplit) + (int64_t)b * kGramExtraRows * a.h;
+  const float* ctx = a.ctx + (int64_t)b * a.h;
   float* C = a.gram + g * a.gram_group_stride;
   auto run = [&](auto cols_c, auto rows_c) {
     using S = GramStrips<decltype(cols_c)::value, decltype(rows_c)::value>;
     gemm_bf16<G, float, GramTokenARows, GramTokenBRows, kEpiNone, S>(
-        ar, br, 2 * n, n, a.h, C, a.gram_ld, m0, n0, smem, nullptr, S{start, cs, n, a.h});
+        ar, br, 2 * n, n, a.h, C, a.gram_ld, m0, n0, smem, nullptr, S{start, ctx, n, a.h});
   };
   using T = std::true_type;
   using F = std::false_type;
@@ -1056,12 +1055,11 @@ __global__ __launch_bounds__(kThreads) void gram_gemm_f32_kernel(GramArgs a, int
   if (!gram_tile(blockIdx.x, per_group, a.G, xcd_grouped, g, t)) return;
   if (!gram_group_ok(a, g, t, g0, n, b)) return;
   const float* KQV = static_cast<const float*>(a.KQV);
-  const float* cs = static_cast<const float*>(a.csplit) + (int64_t)b * kGramExtraRows * a.h;
   const int64_t M = 2 * (n + 1) + kGramExtraRows, N = n + 2;
   const int64_t nt = (a.max_group + 2 + G::BN - 1) / G::BN;
   const int64_t m0 = (t / nt) * G::BM, n0 = (t % nt) * G::BN;
   if (m0 >= M || n0 >= N) return;
-  GramARows<float> ar{KQV, g0, n, a.T_vis, a.h, cs};
+  GramARows<float> ar{KQV, g0, n, a.T_vis, a.h, a.ctx + (int64_t)b * a.h};
   GramBRows<float> br{KQV, g0, n, a.T_vis, a.h};
   gemm_f32<G>(ar, br, M, N, a.h, a.gram + g * a.gram_group_stride, a.gram_ld, m0, n0, smem);
 }
@@ -1148,8 +1146,6 @@ hipError_t launch_gram_gemm(const GramArgs& a, hipStream_t stream) {
   const int64_t M = 2 * ((int64_t)a.max_group + 1) + kGramExtraRows, N = a.max_group + 2;
   const int xcd_grouped = a.G >= 8;
   if (a.dtype == SP_BF16) {
-    hipLaunchKernelGGL(ctx_split_kernel<__bf16>, dim3(a.B), dim3(256), 0, stream, a.ctx, a.h,
-                       (__bf16*)a.csplit);
     // The tile that covers the chip's groups in the least time: rounds of 256
     // workgroups, each a fixed part and its area (gram_tile_us).
     const int64_t mg = a.max_group > 0 ? a.max_group : 1;
@@ -1169,8 +1165,6 @@ hipError_t launch_gram_gemm(const GramArgs& a, hipStream_t stream) {
     else if (cb <= ca) launch(gram_gemm_bf16_kernel<TileGramB>, 256, 192);
     else launch(gram_gemm_bf16_kernel<TileGramA>, 128, 256);
   } else {
-    hipLaunchKernelGGL(ctx_split_kernel<float>, dim3(a.B), dim3(256), 0, stream, a.ctx, a.h,
-                       (float*)a.csplit);
     auto launch = [&](auto tile) {
       using G = decltype(tile);
       const int per_group = (int)f32_tiles<G>(M, N);

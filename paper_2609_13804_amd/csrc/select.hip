@@ -1685,7 +1685,6 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
   ga.grp_img = a.grp_img;
   ga.G = a.G;
   ga.max_group = a.max_group;
-  ga.csplit = a.csplit;
   ga.gram = a.gram;
   ga.gram_group_stride = a.gram_group_stride;
   ga.gram_ld = a.gram_ld;

@@ -49,10 +49,10 @@ hipError_t launch_project_gemm(int dtype, const void* X, int64_t T_vis, const vo
                                const void* E, int64_t T_txt, const void* W_text, int d_text, int h,
                                float* tproj, hipStream_t stream);
 // Per-group Gram products of the projected rows (see select.hip for the
-// layout).  The text context of each image is first written as three rows of
-// the working dtype whose sum is exactly the float32 context (csplit,
-// [B][3][h]); they are the last three A-side rows of every group, so the
-// matrix cores also produce the three parts of cK = c [K; k_stop]^T.
+// layout).  The text context of each image enters as three rows of the
+// working dtype whose sum is exactly the float32 context; they are the last three
+// A-side rows of every group, so the matrix cores also produce the three parts of
+// cK = c [K; k_stop]^T.
 struct GramArgs {
   int dtype;
   const void* KQV;
@@ -64,7 +64,6 @@ struct GramArgs {
   const int32_t* grp_img;
   int G;
   int max_group;
-  void* csplit;
   float* gram;
   int64_t gram_group_stride;
   int gram_ld;
@@ -118,7 +117,6 @@ struct SelectArgs {
   float* gram;
   int64_t gram_group_stride;
   int gram_ld;
-  void* csplit;          // [B][3][h] of the working dtype
   int32_t* grp_kept;     // [G, max_cap]
   int32_t* grp_count;    // [G]
   int32_t* err;
