@@ -335,14 +335,18 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
   // half's first matrix instructions and used after its last.
   constexpr int CT = TM / G::WGN > 0 ? TM / G::WGN : 1, RT = (TN + 1) / 2;
   static_assert(!(SC || SR) || (TM % G::WGN == 0 && G::WGM == 2), "strip tiles per wave");
-  [[maybe_unused]] f32x4_t accc[CT], accr[RT], accx = {0.f, 0.f, 0.f, 0.f};
+  // Tiles with registers to spare sum each k-step apart: half the chain, and the
+  // error of the dot products that the strips replaced.
+  constexpr int NS = G::BM == 128 ? 2 : 1;
+  [[maybe_unused]] f32x4_t accc[NS][CT], accr[NS][RT], accx[NS];
   [[maybe_unused]] bf16x8_t xa[CT], xb[RT], xs, xr;
   if constexpr (SC)
 #pragma unroll
-    for (int c = 0; c < CT; ++c) accc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < CT; ++c) accc[0][c] = accc[NS - 1][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   if constexpr (SR)
 #pragma unroll
-    for (int j = 0; j < RT; ++j) accr[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < RT; ++j) accr[0][j] = accr[NS - 1][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  accx[0] = accx[NS - 1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int xaoff = aoff + wn * CT * 16 * kRowBytes;
   auto strip_col = [&](int j) { const int q = wm * RT + j; return q < TN ? q : TN - 1; };
   auto strip_read = [&](int kt, int ks, int abuf, int bbuf) {
@@ -359,15 +363,15 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
       xr = strips.row_frag(smem + G::LDS, l16, k);
     }
   };
-  auto strip_mfma = [&]() {
+  auto strip_mfma = [&](int ks) {
     if constexpr (SC) {
 #pragma unroll
-      for (int c = 0; c < CT; ++c) accc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xs, xa[c], accc[c], 0, 0, 0);
+      for (int c = 0; c < CT; ++c) accc[ks % NS][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xs, xa[c], accc[ks % NS][c], 0, 0, 0);
     }
     if constexpr (SR) {
 #pragma unroll
-      for (int j = 0; j < RT; ++j) accr[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[j], xr, accr[j], 0, 0, 0);
-      if constexpr (SC) accx = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xs, xr, accx, 0, 0, 0);
+      for (int j = 0; j < RT; ++j) accr[ks % NS][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[j], xr, accr[ks % NS][j], 0, 0, 0);
+      if constexpr (SC) accx[ks % NS] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xs, xr, accx[ks % NS], 0, 0, 0);
     }
   };
 
@@ -393,7 +397,7 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
       }
       load(i);
       if constexpr (SC || SR)
-        if (ks == 1 && (i + 1) % (TM / 2) == 0) strip_mfma();
+        if (ks == 1 && (i + 1) % (TM / 2) == 0) strip_mfma(i / (TM / 2));
       __builtin_amdgcn_sched_barrier(0);
     }
     __builtin_amdgcn_s_setprio(0);
@@ -521,14 +525,14 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
   if constexpr (SC) {
 #pragma unroll
     for (int c = 0; c < CT; ++c)
-      strips.store_col(C, ldc, m0 + wm * (G::BM / 2) + 16 * (wn * CT + c) + l16, M, lk, accc[c]);
+      strips.store_col(C, ldc, m0 + wm * (G::BM / 2) + 16 * (wn * CT + c) + l16, M, lk, NS == 2 ? accc[0][c] + accc[NS - 1][c] : accc[0][c]);
   }
   if constexpr (SR) {
 #pragma unroll
     for (int j = 0; j < RT; ++j)
-      strips.store_row(C, ldc, l16, n0 + wn * (G::BN / G::WGN) + 16 * strip_col(j) + 4 * lk, N, accr[j]);
+      strips.store_row(C, ldc, l16, n0 + wn * (G::BN / G::WGN) + 16 * strip_col(j) + 4 * lk, N, NS == 2 ? accr[0][j] + accr[NS - 1][j] : accr[0][j]);
     if constexpr (SC)
-      if (wave == 0) strips.store_corner(C, ldc, l16, lk, accx);
+      if (wave == 0) strips.store_corner(C, ldc, l16, lk, NS == 2 ? accx[0] + accx[NS - 1] : accx[0]);
   }
 }
 
