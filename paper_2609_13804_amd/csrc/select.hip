@@ -396,9 +396,12 @@ __global__ __launch_bounds__(512) void select_seq_kernel(SelParams p) {
   bool valid = mcol, valid_sec = scol;      // still to be taken
   int kept = 0;
 
-  // Trajectory sums: step t's unnormalised candidate weights stay in registers
-  // while the per-wave partial sums cross the step's barrier; at the top of the
-  // next step every lane adds the partials in wave order.
+  // Trajectory sums: step t's unnormalised candidate weights stay in registers,
+  // and each wave's partial sum goes to its slot of the step's parity after the
+  // step's barrier.  Every lane adds the slots in wave order after step t + 1's
+  // barrier (the one that orders those writes before these reads; the slots are
+  // written again in step t + 2, past its barrier), or after the barrier that
+  // closes the episode.
   const bool traj = TRAJ;
   float tj_A = 1.0f, tj_bt = 1.0f, tj_kbar = 0.0f, tj_s = 0.0f, tj_s2 = 0.0f;
   float tj_e = 0.0f, tj_e2 = 0.0f, tj_estop = 0.0f;
@@ -426,7 +429,6 @@ __global__ __launch_bounds__(512) void select_seq_kernel(SelParams p) {
     constexpr int BK = decltype(bk_c)::value, S = BK / 4, ROW = BK % 4;
     const int pl = (t - 1) - 64 * S;         // the newest entry's lane
     const int par = t & 1;
-    if (traj && tj_t) traj_finish();
 
     // ---- history softmax, by every wave
     float e[S + 1];
@@ -543,6 +545,7 @@ __global__ __launch_bounds__(512) void select_seq_kernel(SelParams p) {
       if (lane == 0) red[par][wave] = make_float4(wbest, __int_as_float(wcol), v2, 0.0f);
     }
     lds_barrier();
+    if (traj && tj_t) traj_finish();
 
     // ---- the decision, by every wave: the largest slot, lowest column on ties
     const float2 s = slot[par][lane & 7];
@@ -1136,10 +1139,12 @@ __global__ __launch_bounds__(MAXT) void select_kernel(SelParams p) {
   int kept = 0;
 
   // Trajectory sums (g = 1, TRAJ kernels): step t's unnormalised candidate
-  // weights e = exp((l - max) / tau) stay in registers while the per-wave
-  // partial sums cross the step's closing barrier; at the top of step t + 1
-  // every lane adds the partials in wave order, and with p_t = e / Z updates
-  // s (its columns), K_bar and A.  Uniform values are kept in every lane.
+  // weights e = exp((l - max) / tau) stay in registers, and each wave's partial
+  // sum goes to its slot of the step's parity after the step's barrier.  After
+  // step t + 1's barrier, which orders those writes before the reads (the slots
+  // are written again past step t + 2's), or the one that closes the episode,
+  // every lane adds the slots in wave order, and with p_t = e / Z updates s (its
+  // columns), K_bar and A.  Uniform values are kept in every lane.
   const bool traj = TRAJ && !GROUPED && p.traj_s != nullptr;
   float tj_A = 1.0f, tj_bt = 1.0f, tj_kbar = 0.0f, tj_s = 0.0f, tj_s2 = 0.0f;
   float tj_e = 0.0f, tj_e2 = 0.0f, tj_estop = 0.0f;
@@ -1164,7 +1169,6 @@ __global__ __launch_bounds__(MAXT) void select_kernel(SelParams p) {
 
   for (int t = 1; t <= cap; ++t) {
     const int par = t & 1;
-    if (traj && tj_pending) traj_finish();
     const float inv = GROUPED ? sm[0] : s_inv, st = GROUPED ? sm[1] : s_st;
     const float e_new = GROUPED ? 0.0f : s_enew;
 
@@ -1478,6 +1482,7 @@ __global__ __launch_bounds__(MAXT) void select_kernel(SelParams p) {
         if (lane == 0) red[par * 16 + wave] = make_float4(vmax, __int_as_float(i1), v2, 0.0f);
       }
       lds_barrier();
+      if (traj && tj_pending) traj_finish();
 
       // ---- the decision: the largest key of the step (every wave reads them all)
       unsigned long long kk = 0ull;
