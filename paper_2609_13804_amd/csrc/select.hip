@@ -1286,17 +1286,20 @@ __global__ __launch_bounds__(MAXT) void select_kernel(SelParams p) {
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
           const int x = u & 3, col = x == 0 ? hc[u >> 2].x : x == 1 ? hc[u >> 2].y : x == 2 ? hc[u >> 2].z : hc[u >> 2].w;
-          // column = row of B; slots past the history repeat an entry, with weight 0
+          // column = row of B; slots past the history repeat an entry
           const int c = __builtin_amdgcn_readfirstlane(tau + u < old ? col : hc[0].x);
           hv[u] = Bm[(int64_t)(c == n + 1 ? n : c) * ld + jc];
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const float4 av = *reinterpret_cast<const float4*>(alphaw + tau + 4 * u);
-          acc = fmaf(tau + 4 * u < old ? av.x : 0.0f, hv[4 * u], acc);
-          acc = fmaf(tau + 4 * u + 1 < old ? av.y : 0.0f, hv[4 * u + 1], acc);
-          acc = fmaf(tau + 4 * u + 2 < old ? av.z : 0.0f, hv[4 * u + 2], acc);
-          acc = fmaf(tau + 4 * u + 3 < old ? av.w : 0.0f, hv[4 * u + 3], acc);
+          // (the terms are dropped, not weighted with 0: a repeated value may be infinite)
+          const float w4[4] = {av.x, av.y, av.z, av.w};
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            const float y = fmaf(w4[x], hv[4 * u + x], acc);
+            acc = tau + 4 * u + x < old ? y : acc;
+          }
         }
       }
     }
