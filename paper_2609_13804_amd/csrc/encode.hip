@@ -358,6 +358,9 @@ __global__ __launch_bounds__(64 * kAttnWaves, SPLIT ? 1 : 2) void attn_kernel(
     }
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
+      // A block past the wave's last key is not weighted with 0: its values may
+      // be infinite or NaN (causal: rows that these queries must not see).
+      if (n > 0 && kb + 32 * n >= kend) break;
       bf16x8_t pb[2];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
