@@ -503,7 +503,10 @@ hipError_t launch_encode(const EncodeArgs& a, hipStream_t stream) {
   const float c2 = 1.4426950408889634f / sqrtf((float)kHead);
   const bool split = split_keys(S, heads, a.causal);
   const int queries = split ? AttnShape<true>::QUERIES : AttnShape<false>::QUERIES;
-  const int q_blocks = (int)(((int64_t)a.max_seq + queries - 1) / queries);
+  // no sequence is longer than the batch, however large a max_seq is passed (the
+  // grid would pass the launch limit)
+  const int64_t longest = a.max_seq < S ? a.max_seq : S;
+  const int q_blocks = (int)((longest + queries - 1) / queries);
   auto* attn = split ? attn_kernel<true> : attn_kernel<false>;
   const dim3 attn_grid((unsigned)((int64_t)q_blocks * heads), (unsigned)a.B);
   for (int k = 0; k < kEncoderBlocks; ++k) {

@@ -1,5 +1,6 @@
 """What an image's encoding must not depend on, to the bit: rows that its
-queries do not see.  Helpers of test_gpu_encoder.py."""
+queries do not see, and how large a max_seq the caller passes.  Helpers of
+test_gpu_encoder.py."""
 import numpy as np
 import pytest
 
@@ -21,3 +22,11 @@ def test_causal_rows_do_not_see_a_later_nan(gpu_lib, rows):
         seen = p // 32 * 32
         np.testing.assert_array_equal(got[:seen], want[:seen])
         assert np.isnan(got[p:]).all()
+
+
+@pytest.mark.parametrize("rows", [300, 2300], ids=["keys_split", "keys_shared"])
+def test_any_max_seq_is_taken(gpu_lib, rows):
+    """A max_seq far past the batch (no limit, to the caller) launches and gives the same bits."""
+    X, img_off, E, text_off, params = _case(62, 512, 128, (rows - 4,), (4,))
+    want = _run(512, 128, X, img_off, E, text_off, params)
+    np.testing.assert_array_equal(_run(512, 128, X, img_off, E, text_off, params, max_seq=2**31 - 1), want)
