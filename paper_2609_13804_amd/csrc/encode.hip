@@ -21,6 +21,8 @@
 // every product's result, the biased q/k/v, the probabilities that weight the
 // values, each head's output, the GELU output and H are bfloat16, rounded
 // once to nearest-even.
+#include <type_traits>
+
 #include "sp_internal.h"
 #include "lds_dma.h"
 #include "row_ops.h"
@@ -35,7 +37,6 @@ typedef __attribute__((address_space(3))) bf16x4_t* ltr_t;
 
 constexpr int kHead = 128;                  // head width
 constexpr int kQPerWave = 32;               // queries of one wave (one 32 x 32 MFMA tile)
-constexpr int kAttnWaves = 4;               // waves of an attention workgroup
 constexpr float kTextLnEps = 1e-5f;
 
 // The image owning row r of a packed array with offsets off[0..B]: the last
@@ -198,11 +199,13 @@ __device__ __forceinline__ float half_sum(float v) {
 // (V, read 64 bytes of four rows at a time).  Keys past the sequence read its
 // last row and are masked.
 //
-// Two splits of the work over a workgroup's four waves:
-//   kShared (SPLIT = false): 128 queries, 32 a wave; the waves share tiles of 64 keys.
-//   kSplit (SPLIT = true): 32 queries; each wave takes every fourth 32-key block through
-//            tiles of its own (no barrier), and the partial sums are combined
-//            through LDS at the end.
+// Two splits of the work over a workgroup's waves:
+//   kShared (SPLIT = false): four waves, 128 queries, 32 a wave; the waves share tiles of 64 keys.
+//   kSplit (SPLIT = true): eight waves, 64 queries, four waves to 32 of them; each of the
+//            four takes every fourth 32-key block of the shared 128-key tiles, and the
+//            partial sums are combined through LDS at the end.  (Four waves and 32
+//            queries a workgroup: one image of 1400 rows at width 1024, causal, 231
+//            against 223 us a pass; 16 of 640 rows 899 against 804.)
 //
 // What bounds it: with 2 x 8 matrix instructions a 32-key block, the softmax's
 // vector instructions (16 exponentials a lane).  So masks are applied only to
@@ -217,24 +220,28 @@ __device__ __forceinline__ float half_sum(float v) {
 // PFLOP/s); one of 1077 rows at width 1024, causal, 50 + 5 -> 17.
 constexpr float kRescale = 8.0f;            // log2 of the largest unscaled probability
 
-template <bool SPLIT>
-struct AttnShape {
-  static constexpr int QUERIES = SPLIT ? kQPerWave : kQPerWave * kAttnWaves;   // of a workgroup
-  static constexpr int TILE = SPLIT ? 32 * kAttnWaves : 64;                    // keys of a tile
-  static constexpr int BLOCKS = SPLIT ? 1 : 2;                                 // 32-key blocks of a step
-  static constexpr int TILE_BYTES = TILE * kHead * 2;                          // K or V
-  static constexpr int LDS = 4 * TILE_BYTES;
-  static constexpr int LOADS = TILE / 4 / kAttnWaves;                          // 4-row groups per wave
-};
 // kSplit's partial sums, over the tiles: 32 rows of 128 values a wave, padded
 constexpr int kPartRow = kHead + 4;
-static_assert(kAttnWaves * kQPerWave * (kPartRow + 2) * 4 <= AttnShape<true>::LDS, "partial sums fit the tiles");
 
 template <bool SPLIT>
-__global__ __launch_bounds__(64 * kAttnWaves, SPLIT ? 1 : 2) void attn_kernel(
+struct AttnShape {
+  static constexpr int WAVES = SPLIT ? 8 : 4, THREADS = 64 * WAVES;
+  static constexpr int SHARES = SPLIT ? 4 : 1;                                 // waves to a query block
+  static constexpr int QUERIES = kQPerWave * WAVES / SHARES;                   // of a workgroup
+  static constexpr int TILE = SPLIT ? 32 * SHARES : 64;                        // keys of a tile
+  static constexpr int BLOCKS = SPLIT ? 1 : 2;                                 // 32-key blocks of a step
+  static constexpr int TILE_BYTES = TILE * kHead * 2;                          // K or V
+  static constexpr int PARTS = SPLIT ? WAVES * kQPerWave * (kPartRow + 2) * 4 : 0;   // partial sums
+  static constexpr int LDS = 4 * TILE_BYTES > PARTS ? 4 * TILE_BYTES : PARTS;
+  static constexpr int LOADS = TILE / 4 / WAVES;                               // 4-row groups per wave
+  static_assert(LDS * (SPLIT ? 1 : 2) <= kLdsBytes, "the tiles and partial sums fit the LDS");
+};
+
+template <bool SPLIT>
+__global__ __launch_bounds__(AttnShape<SPLIT>::THREADS, SPLIT ? 1 : 2) void attn_kernel(
     const uint16_t* __restrict__ QKV, int d, int q_blocks, const int32_t* __restrict__ img_off,
-    const int32_t* __restrict__ text_off, int max_seq, int64_t S_total, int causal, float c2,
-    uint16_t* __restrict__ O, int32_t* err) {
+    const int32_t* __restrict__ text_off, int max_seq, int64_t S_total, int split_rows, int causal,
+    float c2, uint16_t* __restrict__ O, int32_t* err) {
   using G = AttnShape<SPLIT>;
   constexpr int NB = G::BLOCKS;
   __shared__ __attribute__((aligned(1024))) char smem[G::LDS];   // [buffer][K, V]
@@ -257,8 +264,9 @@ __global__ __launch_bounds__(64 * kAttnWaves, SPLIT ? 1 : 2) void attn_kernel(
   int S;
   if (!sequence_of(img_off, text_off, b, max_seq, S_total, so, S, err, tid == 0 && w == 0)) return;
   const int qw = qb * G::QUERIES;                                   // the workgroup's first query
-  if (qw >= S) return;
-  const int q0 = SPLIT ? qw : qw + wave * kQPerWave;                // this wave's (may be past S)
+  if (qw >= S || (S <= split_rows) != SPLIT) return;
+  // this wave's first query (may be past S) and, kSplit, its share of the keys
+  const int q0 = qw + wave / G::SHARES * kQPerWave, share = wave % G::SHARES;
   const int ql = lane & 31, half = lane >> 5;
   const int64_t ld = 3 * (int64_t)d;
   const uint16_t* Qb = QKV + so * ld + hd * kHead;
@@ -276,7 +284,7 @@ __global__ __launch_bounds__(64 * kAttnWaves, SPLIT ? 1 : 2) void attn_kernel(
 
   // Tile loads: an instruction fills 1 KB, 4 rows; lane i lands on chunk i % 16
   // of row i / 16, so it fetches the logical chunk that the swizzle puts there.
-  // kSplit: the wave's own 32 rows; kShared: row groups wave, wave + 4, ...
+  // The wave loads row groups wave, wave + WAVES, ...
   const int lrow = lane >> 4, lch = lane & 15;
   auto issue_tile = [&](int kt, int buf) {
     const int k0 = kt * G::TILE;
@@ -289,7 +297,7 @@ __global__ __launch_bounds__(64 * kAttnWaves, SPLIT ? 1 : 2) void attn_kernel(
     char* dst = smem + buf * 2 * G::TILE_BYTES;
 #pragma unroll
     for (int i = 0; i < G::LOADS; ++i) {
-      const int grp = SPLIT ? wave * G::LOADS + i : wave + kAttnWaves * i;
+      const int grp = wave + G::WAVES * i;
       const int r = 4 * grp + lrow;
       const uint32_t row = (uint32_t)(r < last ? r : last) * (uint32_t)(2 * ld);
       lds_dma16(Kt, row + ((lch ^ (r & 15)) << 4), dst + grp * 1024);
@@ -380,39 +388,20 @@ __global__ __launch_bounds__(64 * kAttnWaves, SPLIT ? 1 : 2) void attn_kernel(
   };
 
   issue_tile(0, 0);
-  if constexpr (SPLIT) {
-    const int row = 32 * wave;
-    for (int kt = 0; kt < tiles; ++kt) {
-      const int buf = kt & 1;
-      if (kt + 1 < tiles) {
-        wait_lgkm0();                        // this wave's reads of the other buffer
-        issue_tile(kt + 1, buf ^ 1);
-        wait_vmcnt<2 * G::LOADS>();          // tile kt has landed
-      } else {
-        wait_vmcnt<0>();
-      }
-      asm volatile("" ::: "memory");
-      const int kb = kt * G::TILE + row;
-      if (kb < kend) step(buf, row, kb);     // uniform in the wave
-    }
-  } else {
-    wait_vmcnt<0>();
-    __syncthreads();
-    for (int kt = 0; kt < tiles; ++kt) {
-      const int buf = kt & 1;
-      // the other buffer was last read before the previous barrier
-      if (kt + 1 < tiles) issue_tile(kt + 1, buf ^ 1);
-      if (kt * G::TILE < kend) step(buf, 0, kt * G::TILE);
-      wait_vmcnt<0>();                       // this wave's loads of the next tile
-      __syncthreads();
-    }
+  for (int kt = 0; kt < tiles; ++kt) {
+    const int buf = kt & 1;
+    wait_vmcnt<0>();                         // this wave's loads of tile kt
+    __syncthreads();                         // every wave's; and all are past tile kt - 1
+    if (kt + 1 < tiles) issue_tile(kt + 1, buf ^ 1);
+    const int kb = kt * G::TILE + 32 * share;
+    if (kb < kend) step(buf, 32 * share, kb);   // uniform in the wave
   }
   l = half_sum(l);
 
   // O^T[e][q] in o[t][r]: e = 32 t + 8 (r / 4) + 4 (l / 32) + r % 4
   if constexpr (SPLIT) {
     float* part = reinterpret_cast<float*>(smem);                   // [wave][query][kPartRow]
-    float* ml = part + kAttnWaves * kQPerWave * kPartRow;            // [m, l][wave][query]
+    float* ml = part + G::WAVES * kQPerWave * kPartRow;              // [m, l][wave][query]
     __syncthreads();                                                 // every wave is past its tiles
 #pragma unroll
     for (int t = 0; t < kHead / 32; ++t)
@@ -422,26 +411,28 @@ __global__ __launch_bounds__(64 * kAttnWaves, SPLIT ? 1 : 2) void attn_kernel(
             make_float4(o[t][4 * g4], o[t][4 * g4 + 1], o[t][4 * g4 + 2], o[t][4 * g4 + 3]);
     if (half == 0) {
       ml[wave * kQPerWave + ql] = m;
-      ml[(kAttnWaves + wave) * kQPerWave + ql] = l;
+      ml[(G::WAVES + wave) * kQPerWave + ql] = l;
     }
     __syncthreads();
-    const int cq = tid >> 3, e0 = (tid & 7) * 16;                    // 16 values of one query a thread
-    if (qw + cq >= S) return;
+    // 16 values of one query a thread, of the query block's waves w0 ..
+    const int cq = (tid >> 3) % kQPerWave, e0 = (tid & 7) * 16, w0 = tid / (8 * kQPerWave) * G::SHARES;
+    const int qc = qw + tid / 8;
+    if (qc >= S) return;
     float M = -INFINITY;
 #pragma unroll
-    for (int v = 0; v < kAttnWaves; ++v) M = fmaxf(M, ml[v * kQPerWave + cq]);
+    for (int v = 0; v < G::SHARES; ++v) M = fmaxf(M, ml[(w0 + v) * kQPerWave + cq]);
     float L = 0.0f, acc[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
 #pragma unroll
-    for (int v = 0; v < kAttnWaves; ++v) {
+    for (int v = 0; v < G::SHARES; ++v) {
       // a wave without keys has m = -inf and zero sums
-      const float mv = ml[v * kQPerWave + cq];
+      const float mv = ml[(w0 + v) * kQPerWave + cq];
       const float f = mv == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mv - M);
-      L = fmaf(ml[(kAttnWaves + v) * kQPerWave + cq], f, L);
+      L = fmaf(ml[(G::WAVES + w0 + v) * kQPerWave + cq], f, L);
 #pragma unroll
       for (int e = 0; e < 16; e += 4) {
-        const float4 x = *reinterpret_cast<const float4*>(part + (v * kQPerWave + cq) * kPartRow + e0 + e);
+        const float4 x = *reinterpret_cast<const float4*>(part + ((w0 + v) * kQPerWave + cq) * kPartRow + e0 + e);
         acc[e] = fmaf(x.x, f, acc[e]);
         acc[e + 1] = fmaf(x.y, f, acc[e + 1]);
         acc[e + 2] = fmaf(x.z, f, acc[e + 2]);
@@ -454,7 +445,7 @@ __global__ __launch_bounds__(64 * kAttnWaves, SPLIT ? 1 : 2) void attn_kernel(
     for (int e = 0; e < 16; e += 8) {
 #pragma unroll
       for (int k = 0; k < 8; ++k) out[k] = acc[e + k] * inv;
-      store8(O + (so + qw + cq) * d + hd * kHead + e0 + e, out);
+      store8(O + (so + qc) * d + hd * kHead + e0 + e, out);
     }
   } else {
     if (q >= S) return;
@@ -472,16 +463,14 @@ __global__ __launch_bounds__(64 * kAttnWaves, SPLIT ? 1 : 2) void attn_kernel(
   }
 }
 
-// Attention takes kSplit while its workgroups (32 queries of a head; S rows in
-// the batch) fit one round of the 256 compute units, or one and a half when
-// causal, where the later ones have few keys.  us, kShared against kSplit, at
-// workgroups of kSplit: 160 17.9 / 11.5, 182 13.4 / 8.7, 264 19.2 / 22.7, 320
-// 17.9 / 20.4; causal: 276 26.9 / 17.4, 320 18.2 / 12.2, 384 16.7 / 15.6, 640
-// 18.9 / 22.5.  Counted from the batch's rows, so that neither the choice nor
-// the order of the sums depends on the max_seq that a caller passes.
-inline bool split_keys(int64_t S, int heads, bool causal) {
-  return S * heads <= (causal ? 384 : 256) * (int64_t)kQPerWave;
-}
+// Sequences of up to this many rows take kSplit: while their 32-query blocks of
+// all heads are at most one to a compute unit, or one and a half when causal,
+// where the later ones have few keys.  us a pass of one image, kShared against
+// kSplit: 640 rows at width 1024 167 / 157, 2048 rows at width 512 188 / 155; causal
+// at width 1024, 1077 rows 219 / 204, 1536 rows 255 / 230.  A sequence's own length
+// decides, so that its rows have the same bits alone and in any batch; in a batch
+// that fills the chip kShared would be faster (16 x 640 rows at width 1024 776 / 807).
+inline int split_limit(int heads, bool causal) { return (causal ? 384 : 256) * kQPerWave / heads; }
 
 }  // namespace
 
@@ -501,22 +490,28 @@ hipError_t launch_encode(const EncodeArgs& a, hipStream_t stream) {
                      a.HID, a.T_txt, d, a.img_off, a.text_off, a.B, a.g_text, a.blk[0].ln1_g,
                      a.blk[0].ln1_b, a.R, a.L, a.err);
   const float c2 = 1.4426950408889634f / sqrtf((float)kHead);
-  const bool split = split_keys(S, heads, a.causal);
-  const int queries = split ? AttnShape<true>::QUERIES : AttnShape<false>::QUERIES;
   // no sequence is longer than the batch, however large a max_seq is passed (the
   // grid would pass the launch limit)
   const int64_t longest = a.max_seq < S ? a.max_seq : S;
-  const int q_blocks = (int)((longest + queries - 1) / queries);
-  auto* attn = split ? attn_kernel<true> : attn_kernel<false>;
-  const dim3 attn_grid((unsigned)((int64_t)q_blocks * heads), (unsigned)a.B);
+  const int limit = split_limit(heads, a.causal);
+  // The shortest sequence has at least the rows that B - 1 of the longest leave:
+  // past the limit, all of them are shared, and the launch for the others is saved.
+  const int split_rows = S - (a.B - 1) * longest > limit ? 0 : limit;
+  auto attention = [&](auto split_c, int64_t rows) {
+    using G = AttnShape<decltype(split_c)::value>;
+    const int64_t q_blocks = (rows + G::QUERIES - 1) / G::QUERIES;
+    hipLaunchKernelGGL(attn_kernel<decltype(split_c)::value>, dim3((unsigned)(q_blocks * heads), (unsigned)a.B),
+                       dim3(G::THREADS), 0, stream, a.QKV, d, (int)q_blocks, a.img_off, a.text_off,
+                       a.max_seq, S, split_rows, a.causal ? 1 : 0, c2, a.A, a.err);
+  };
   for (int k = 0; k < kEncoderBlocks; ++k) {
     const EncoderBlockArgs& p = a.blk[k];
     // q, k, v of LN1(R) (in L), biased in the product's epilogue
     if ((e = launch_dense_bf16(a.L, p.W_qkv, S, 3 * (int64_t)d, d, a.QKV, stream, p.b_qkv)) !=
         hipSuccess)
       return e;
-    hipLaunchKernelGGL(attn, attn_grid, dim3(64 * kAttnWaves), 0, stream, a.QKV, d, q_blocks,
-                       a.img_off, a.text_off, a.max_seq, S, a.causal ? 1 : 0, c2, a.A, a.err);
+    if (longest > split_rows) attention(std::false_type{}, longest);
+    if (split_rows > 0) attention(std::true_type{}, longest < split_rows ? longest : split_rows);
     // R += A W_o^T + b_o; LN2 into A
     if ((e = launch_dense_bf16(a.A, p.W_o, S, d, d, a.L, stream)) != hipSuccess) return e;
     if ((e = launch_resid_ln(a.R, a.L, p.b_o, S, d, p.ln2_g, p.ln2_b, a.A, stream)) != hipSuccess)
