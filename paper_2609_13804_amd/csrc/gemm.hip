@@ -331,47 +331,65 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
   // Strips: the column strip's 16 x 16 tiles are shared out over the waves (CT
   // row groups of the wave's own half each), the row strip's likewise (RT column
   // groups).  Their fragments are read and used within phase 0, for both k-steps
-  // (the stage's buffers are free after it): k-step ks is read before the
-  // half's first matrix instructions and used after its last.
-  constexpr int CT = TM / G::WGN > 0 ? TM / G::WGN : 1, RT = (TN + 1) / 2;
-  static_assert(!(SC || SR) || (TM % G::WGN == 0 && G::WGM == 2), "strip tiles per wave");
-  // Tiles with registers to spare sum each k-step apart: half the chain, and the
-  // error of the dot products that the strips replaced.
-  constexpr int NS = G::BM == 128 ? 2 : 1;
-  [[maybe_unused]] f32x4_t accc[NS][CT], accr[NS][RT], accx[NS];
+  // (the stage's buffers are free after it), in four slots of TM / 4 groups: the
+  // columns' two k-steps, then the rows': read before the slot's first matrix
+  // instructions and used after its last.  A stage's two products are one chain in
+  // float32; the stages are added in 64 bits, in order, so that the sums do not
+  // depend on the tile and are as close as the dot products of 64 lanes that the
+  // strips replaced.  Against 64 bits (normal operands, 2-norm), 256-token groups, h
+  // 640 / 512-token groups, h 512 / 768-token groups, h 1024: 6.5e-8 / 6.1e-8 /
+  // 6.8e-8 with the dot products, 1.0e-7 / 8.7e-8 / 1.9e-7 as one or two chains over
+  // K, 5.0e-8 in all of them now, for 1 us of a tile's time.  A lane's results repeat those of
+  // the lanes beside it, so each sums other registers, and ten hold all the sums.
+  constexpr int CT = TM / G::WGN > 0 ? TM / G::WGN : 1, RT = (TN + 1) / 2, SLOT = TM / 4;
+  static_assert(!(SC || SR) || (TM % 4 == 0 && CT <= 2 && RT == 2 && G::WGM == 2), "strip tiles per wave");
+  [[maybe_unused]] f32x4_t accc[CT], accr[RT], accx;
+  [[maybe_unused]] double sumc = 0.0, sumr[3] = {0.0, 0.0, 0.0}, sumx = 0.0;
   [[maybe_unused]] bf16x8_t xa[CT], xb[RT], xs, xr;
-  if constexpr (SC)
-#pragma unroll
-    for (int c = 0; c < CT; ++c) accc[0][c] = accc[NS - 1][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  if constexpr (SR)
-#pragma unroll
-    for (int j = 0; j < RT; ++j) accr[0][j] = accr[NS - 1][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  accx[0] = accx[NS - 1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int xaoff = aoff + wn * CT * 16 * kRowBytes;
   auto strip_col = [&](int j) { const int q = wm * RT + j; return q < TN ? q : TN - 1; };
-  auto strip_read = [&](int kt, int ks, int abuf, int bbuf) {
-    const int k = kt * kKStage + ks * 32 + 8 * lk;
-    if constexpr (SC) {
+  auto strip_read = [&](int kt, int slot, int abuf, int bbuf) {
+    const int ks = slot & 1, k = kt * kKStage + ks * 32 + 8 * lk;
+    if constexpr (SC)
+      if (slot < 2) {
 #pragma unroll
-      for (int c = 0; c < CT; ++c) xa[c] = frag(abuf, xaoff, ks, c);
-    }
-    if constexpr (SC) xs = strips.col_frag(smem + G::LDS, l16, k);
-    if constexpr (SR) {
+        for (int c = 0; c < CT; ++c) xa[c] = frag(abuf, xaoff, ks, c);
+      }
+    if constexpr (SC)
+      if (slot < 2 || SR) xs = strips.col_frag(smem + G::LDS, l16, k);
+    if constexpr (SR)
+      if (slot >= 2) {
 #pragma unroll
-      for (int j = 0; j < RT; ++j)
-        xb[j] = *reinterpret_cast<const bf16x8_t*>(smem + bbuf + (boff ^ (ks << 6)) + strip_col(j) * 16 * kRowBytes);
-      xr = strips.row_frag(smem + G::LDS, l16, k);
-    }
+        for (int j = 0; j < RT; ++j)
+          xb[j] = *reinterpret_cast<const bf16x8_t*>(smem + bbuf + (boff ^ (ks << 6)) + strip_col(j) * 16 * kRowBytes);
+        xr = strips.row_frag(smem + G::LDS, l16, k);
+      }
   };
-  auto strip_mfma = [&](int ks) {
-    if constexpr (SC) {
+  auto strip_mfma = [&](int slot) {
+    auto add = [&](bf16x8_t x, bf16x8_t y, f32x4_t& v) {
+      v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, slot & 1 ? v : f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    };
+    if constexpr (SC)
+      if (slot < 2) {
 #pragma unroll
-      for (int c = 0; c < CT; ++c) accc[ks % NS][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xs, xa[c], accc[ks % NS][c], 0, 0, 0);
-    }
+        for (int c = 0; c < CT; ++c) add(xs, xa[c], accc[c]);
+      }
+    if constexpr (SR)
+      if (slot >= 2) {
+#pragma unroll
+        for (int j = 0; j < RT; ++j) add(xb[j], xr, accr[j]);
+        if constexpr (SC) add(xs, xr, accx);
+      }
+  };
+  // The stage's sums, a slot or a phase after their last products.
+  auto strip_sum_cols = [&]() {
+    if constexpr (SC) sumc += (double)Strips::col_value(accc[0], accc[CT - 1], lk);
+  };
+  auto strip_sum_rows = [&]() {
     if constexpr (SR) {
 #pragma unroll
-      for (int j = 0; j < RT; ++j) accr[ks % NS][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[j], xr, accr[ks % NS][j], 0, 0, 0);
-      if constexpr (SC) accx[ks % NS] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xs, xr, accx[ks % NS], 0, 0, 0);
+      for (int i = 0; i < 3; ++i) sumr[i] += (double)Strips::row_value(accr[0], accr[1], i, l16);
+      if constexpr (SC) sumx += (double)(lk & 1 ? accx[1] : accx[0]);
     }
   };
 
@@ -382,8 +400,11 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
     __builtin_amdgcn_s_setprio(1);   // the wave whose operands are ready goes first
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      if constexpr (SC || SR)
-        if (ks == 1 && i % (TM / 2) == 0) strip_read(kt, i / (TM / 2), abuf, bbuf);
+      if constexpr (SC || SR) {
+        if (ks == 1 && i % SLOT == 0) strip_read(kt, i / SLOT, abuf, bbuf);
+        if (ks == 1 && i == 2 * SLOT) strip_sum_cols();
+        if (ks == 0 && i == 1) strip_sum_rows();
+      }
 #pragma unroll
       for (int j = 0; j < TN; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.b[j], cur.a[i], acc[i][j], 0, 0, 0);
@@ -397,7 +418,7 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
       }
       load(i);
       if constexpr (SC || SR)
-        if (ks == 1 && (i + 1) % (TM / 2) == 0) strip_mfma(i / (TM / 2));
+        if (ks == 1 && (i + 1) % SLOT == 0) strip_mfma(i / SLOT);
       __builtin_amdgcn_sched_barrier(0);
     }
     __builtin_amdgcn_s_setprio(0);
@@ -522,17 +543,17 @@ __device__ __forceinline__ void gemm_bf16(const ARows& ar, const BRows& br, int6
     }
     if (p + 1 < PASSES) __syncthreads();
   }
-  if constexpr (SC) {
-#pragma unroll
-    for (int c = 0; c < CT; ++c)
-      strips.store_col(C, ldc, m0 + wm * (G::BM / 2) + 16 * (wn * CT + c) + l16, M, lk, NS == 2 ? accc[0][c] + accc[NS - 1][c] : accc[0][c]);
-  }
+  if constexpr (SC)
+    if (lk < 2 * CT) strips.store_col(C, ldc, m0 + wm * (G::BM / 2) + 16 * (wn * CT + lk / 2) + l16, M, lk & 1, (float)sumc);
   if constexpr (SR) {
 #pragma unroll
-    for (int j = 0; j < RT; ++j)
-      strips.store_row(C, ldc, l16, n0 + wn * (G::BN / G::WGN) + 16 * strip_col(j) + 4 * lk, N, NS == 2 ? accr[0][j] + accr[NS - 1][j] : accr[0][j]);
+    for (int i = 0; i < 3; ++i) {
+      const int u = Strips::row_slot(i, l16);            // register u % 4 of column group u / 4
+      if (u < 4 * RT)
+        strips.store_row(C, ldc, l16, n0 + wn * (G::BN / G::WGN) + 16 * strip_col(u / 4) + 4 * lk + u % 4, N, (float)sumr[i]);
+    }
     if constexpr (SC)
-      if (wave == 0) strips.store_corner(C, ldc, l16, lk, NS == 2 ? accx[0] + accx[NS - 1] : accx[0]);
+      if (wave == 0 && lk < 2 && l16 < 5) strips.store_corner(C, ldc, l16, lk, (float)sumx);
   }
 }
 
@@ -771,34 +792,34 @@ struct GramStrips {
   __device__ bf16x8_t at(const char* s, int r, int k) const {
     return *reinterpret_cast<const bf16x8_t*>(s + r * stride() + 2 * k);
   }
-  __device__ bf16x8_t row_frag(const char* s, int l16, int k) const { return at(s, l16 < 5 ? l16 : 4, k); }
+  __device__ bf16x8_t row_frag(const char* s, int l16, int k) const { return at(s, l16 % 5, k); }
   __device__ bf16x8_t col_frag(const char* s, int l16, int k) const { return at(s, 5 + (l16 & 1), k); }
+  // Which result a lane sums.  Columns: every lane of token row l16 holds [k_stop,
+  // k_start] in registers 0 and 1 of each row group; lane quarter lk takes column
+  // lk % 2 of group lk / 2.  Rows: lanes l16 % 5 hold eight columns, four registers
+  // of two column groups; fifth l16 / 5 of a row takes registers l16 / 5, + 3, + 6.
+  __device__ static float col_value(f32x4_t g0, f32x4_t g1, int lk) {
+    const float a = lk & 2 ? g1[0] : g0[0], b = lk & 2 ? g1[1] : g0[1];
+    return lk & 1 ? b : a;
+  }
+  __device__ static int row_slot(int i, int l16) { return l16 < 15 ? l16 / 5 + 3 * i : 8; }
+  __device__ static float row_value(f32x4_t g0, f32x4_t g1, int i, int l16) {
+    auto at = [&](int u) { return u < 4 ? g0[u % 4] : g1[u % 4]; };
+    const float a = at(3 * i), b = at(3 * i + 1), c = at(3 * i + 2 < 8 ? 3 * i + 2 : 7);
+    return l16 < 5 ? a : l16 < 10 ? b : c;
+  }
   // The block's rows: A of the tokens, A of START, B of the tokens, B of START,
   // the three context rows.
   __device__ int64_t out_row(int64_t r) const { return r < n ? r : r + 1; }
   __device__ int64_t strip_row(int r) const { return r == 0 ? n : 2 * n + r; }
-  __device__ void store_col(float* C, int64_t ldc, int64_t row, int64_t M, int lk, f32x4_t v) const {
-    if (lk != 0 || row >= M) return;
-    float* dst = C + out_row(row) * ldc + n;
-    dst[0] = v[0];
-    dst[1] = v[1];
+  __device__ void store_col(float* C, int64_t ldc, int64_t row, int64_t M, int c, float v) const {
+    if (row < M) C[out_row(row) * ldc + n + c] = v;
   }
-  __device__ void store_row(float* C, int64_t ldc, int r, int64_t col, int64_t N, f32x4_t v) const {
-    if (r >= 5) return;
-    float* dst = C + strip_row(r) * ldc + col;             // 16-byte aligned: ldc and col are multiples of 4
-    if (col + 4 <= N) {
-      *reinterpret_cast<f32x4_t*>(dst) = v;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (col + e < N) dst[e] = v[e];
-    }
+  __device__ void store_row(float* C, int64_t ldc, int l16, int64_t col, int64_t N, float v) const {
+    if (col < N) C[strip_row(l16 % 5) * ldc + col] = v;
   }
-  __device__ void store_corner(float* C, int64_t ldc, int r, int lk, f32x4_t v) const {
-    if (r >= 5 || lk != 0) return;
-    float* dst = C + strip_row(r) * ldc + n;
-    dst[0] = v[0];
-    dst[1] = v[1];
+  __device__ void store_corner(float* C, int64_t ldc, int r, int c, float v) const {
+    C[strip_row(r) * ldc + n + c] = v;
   }
 };
 
