@@ -206,18 +206,21 @@ using TileGramC = BfTile<128, 192, 2, 4, 2>;     // 96 KB
 
 // Output epilogue of the bfloat16 core: the product as it is, or (bfloat16
 // output only) the product rounded to bfloat16, plus a per-column float32 bias,
-// optionally through the exact GELU, rounded again: the same values as storing
-// the product and then running a bias (+ GELU) pass over it.
+// optionally through the GELU (below), rounded again: the same values as storing
+// the product and then running a bias (+ GELU) pass of this arithmetic over it.
 constexpr int kEpiNone = 0, kEpiBias = 1, kEpiBiasGelu = 2;
 
-// The exact GELU, y Phi(y), in float32: Phi(-a) = exp2(-a^2 log2(e) / 2 + g(a))
-// for a = |y|, g = log2 of half the scaled complementary error function of
-// a / sqrt(2), a smooth function that a degree-9 polynomial in 2 a / 5 - 1 (a
-// weighted minimax fit over [0, 5]) gives within 1e-6 of Phi's tail; past 5,
-// where Phi(-a) < 3e-7, g stays as it is at 5.  Against 64 bits, 3e6 values
-// (N(0, 1) and uniform over [-8, 8]): 2-norm 2.2e-8 of the result's and at most
-// 2e-6 of a value, where y (1 + erf(y / sqrt 2)) / 2 with a correctly rounded
-// erf is off by 2.3e-8 and, in the tail, whole values.
+// The GELU, y Phi(y), in float32: Phi(-a) = exp2(-a^2 log2(e) / 2 + g(a)) for a =
+// |y|, g = log2 of half the scaled complementary error function of a / sqrt(2), a
+// smooth function for which a degree-9 polynomial in 2 a / 5 - 1 stands (weighted
+// minimax fit over [0, 5]: least squares at Chebyshev nodes, the weights raised
+// where the error in Phi(-a), or in 0.02 of it for small ones, is largest); past 5
+// g stays as it is at 5.  Against 64 bits: at most 2.6e-6 of a value for y > -5,
+// and 2e-8 past it, where the GELU itself is below 1.5e-6 and g should still fall
+// (0.1 of a value at -5.5, 0.6 at -8); y (1 + erf(y / sqrt 2)) / 2 with a correctly
+// rounded erf is off by up to 5 % of a value in [-5, -4], 8e-8 past -5 (whole
+// values).  2-norm of the error over that of the result, for normal y / for y
+// uniform over [-8, 8]: 4.3e-8 / 1.9e-8, and 3.8e-8 / 2.1e-8 that way.
 // A wave's epilogue is bound by these instructions, which no matrix work
 // hides: about 20 a value where the library's erff took twice as many.  A pass
 // of the denoiser (9216 x 16384 x 4096 with bias and GELU in it) 2663 -> 2474 us,
