@@ -218,8 +218,8 @@ sp_status stepprune_select(const sp_dims* dims,
  * stepprune_select for callers that cannot allocate device memory (code under
  * HIP graph capture, serving loops or harnesses that forbid allocation): the
  * same selection, decisions and outputs, with no caller workspace.  The
- * scratch (the Gram blocks, the context split and the group-local kept lists
- * that stepprune_select keeps in `ws`) is a fixed array of
+ * scratch (the Gram blocks and the group-local kept lists that
+ * stepprune_select keeps in `ws`) is a fixed array of
  * STEPPRUNE_NOALLOC_SCRATCH_BYTES in the library's device memory, one copy per
  * GPU, held until the process ends.  The call itself allocates nothing; its
  * first call on a GPU looks up that GPU's copy.

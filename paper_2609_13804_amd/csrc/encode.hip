@@ -216,7 +216,7 @@ __device__ __forceinline__ float half_sum(float v) {
 //
 // us at width 4096 (32 heads) against a kernel with masks, a rescale and
 // shuffles at every step, values transposed by a kernel before it, and 128
-// queries a workgroup only: 16 sequences of 640 rows 246 + 50 -> 140 (0.77
+// queries a workgroup only: 16 sequences of 640 rows 239 + 50 -> 160 (0.67
 // PFLOP/s); one of 1077 rows at width 1024, causal, 50 + 5 -> 17.
 constexpr float kRescale = 8.0f;            // log2 of the largest unscaled probability
 

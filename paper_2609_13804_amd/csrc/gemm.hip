@@ -167,9 +167,10 @@ __device__ __forceinline__ void gemm_f32(const ARows& ar, const BRows& br, int64
 //    sustain 1.79 PFLOP/s with the 32x32x16 instruction and 2.07 with 16x16x32
 //    (2.45 with zeros): half the accumulator traffic per flop;
 //  * barriers: one per stage, in its middle (below).
-// A core of 32-wide stages and 32x32x16 instructions took 1001 us (1.24 PFLOP/s)
-// where this one takes 864 (1.43), with bit-identical results; on 8192 x 8192 x
-// 4096 444 against 378 us.
+// Within a pass of the denoiser a core of 32-wide stages and 32x32x16 instructions
+// with whole tiles only took 1341 us for it (0.92 PFLOP/s) and this one takes 998
+// (1.24), with bit-identical results; 10240 rows in the encoder 1320 against 976 to
+// 993 (1.40).
 //
 // A 128-byte row holds eight 16-byte chunks, chunk c of row r at slot
 // c ^ ((r >> 1) & 7), which the load realises by choosing each lane's source
@@ -1026,8 +1027,8 @@ __device__ __forceinline__ bool gram_group_ok(const GramArgs& a, int64_t g, int6
 // five rows and two columns beside them.  Measured against whole 256 x 256 tiles
 // over [Q; q_start; V; v_start; c] x [K; k_stop; k_start] (for groups just below
 // a multiple of 256: tiles over the tokens, and dot products in a second kernel
-// that read every row again), h 1024: 832 groups of 256 713 -> 421 us, 157
-// groups of 388-576 322 -> 272, 40 of 576 103 -> 85, 5 of 576 36 -> 23.
+// that read every row again), h 1024: 832 groups of 256 713 -> 418 us, 40 of 576 108
+// -> 83, 20 of 1000 130 -> 131, 5 of 576 36 -> 23; 16 of 576, h 640, 33.6 -> 29.7.
 template <class G>
 __global__ __launch_bounds__(kBfThreads) void gram_gemm_bf16_kernel(GramArgs a, int per_group,
                                                                     int xcd_grouped) {
@@ -1115,8 +1116,9 @@ int text_split(int dtype, int64_t T_txt, int h, int d_text) {
   // pooling at 1, 2, 4 and 8 parts (image rows, text rows, d, h): 576, 32, 1024, 256
   // 20.8, 21.1, 21.5, 23.0; 300, 128, 1024, 512 27.9, 23.5, 22.5, 22.9; 2000, 400, 1536,
   // 320 92, 80, 73, 71; 4096, 2048, 1024, 512 155, 148, 147, 152; no image rows, 2048,
-  // 1024, 512 48, 44, 44, 52: 8 parts cost up to 18 % on the least product, and save up
-  // to 23 %.  The workspace's size and the order of the sums follow the parts.
+  // 1024, 512 48, 44, 44, 52: the rule's choice, 8 in all of these, is up to 18 % from
+  // the best and up to 23 % better than one.  The workspace's size and the order of
+  // the sums follow the parts.
   const int64_t tiles = ceil_div(T_txt, 128) * ceil_div(h, 128);
   int s = 1;
   while (s < 8 && tiles * s < 512 && d_text % (2 * s * 64) == 0) s *= 2;

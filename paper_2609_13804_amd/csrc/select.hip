@@ -12,8 +12,8 @@
 // contractions computed once per group on the matrix cores (gemm.hip), so a
 // step needs only the row A[e, :] and the column values B[e, j] of the newest
 // history entry e: one dependent load, then O(t * n) float32 FMAs.  One
-// workgroup runs one episode end to end (select_kernel below), so no step
-// ever leaves the compute unit.
+// workgroup runs one episode end to end (select_seq_kernel and select_kernel
+// below), so no step ever leaves the compute unit.
 //
 // Gram layout per group (float32, row stride ld): rows [0, n) A rows of the
 // tokens, row n the A row of START, rows [n+1, 2n+1) B rows of the tokens,
@@ -694,14 +694,15 @@ __global__ __launch_bounds__(512) void select_seq_kernel(SelParams p) {
 // product of the weights with the STOP column of the history rows, reduced
 // inside the softmax.
 //
-// A step: every wave computes its columns' logits from the softmax weights in
-// LDS and folds its best candidate into the step's decision key (a 64-bit LDS
-// atomic max of value bits and inverted index, so ties go to the lower index
-// and STOP, index n, loses them); barrier; every wave reads the same decision;
-// each thread loads the chosen row's A and B values of its columns, and wave
-// 0 gathers the history scores from the chosen A row and writes the next
-// softmax into LDS; barrier.  The B values are first needed at the end of the
-// next step's logits, after the older history terms.
+// One token a round: every wave computes its columns' logits from its own copy of
+// the softmax weights and writes its best candidate's key (value bits, then the
+// inverted index, so ties go to the lower index; wave 0 folds in STOP, index n,
+// which loses them) into the step's slots; the step's one barrier; every wave
+// takes the largest key, loads the chosen row's A and B values of its columns,
+// gathers the history scores from the chosen A row and computes the next softmax
+// for itself.  The slots alternate by step parity: they are written again past the
+// next barrier, when every wave has read them.  The B values are first needed at
+// the end of the next step's logits, after the older history terms.
 //
 // Grouped kernels (GMAX > 1, Eq. 11) keep g tokens per round: the newest
 // history entries are a group of ng tokens whose mean query row drives the
@@ -709,7 +710,8 @@ __global__ __launch_bounds__(512) void select_seq_kernel(SelParams p) {
 // scores and the A term of the logits are means too); each wave then finds
 // its g best candidates, writes their keys to LDS, and after the barrier
 // every wave ranks all of them the same way, stops if STOP's key beats the
-// best, and otherwise takes the g best as the round's group.
+// best, and otherwise takes the g best as the round's group; wave 0 alone gathers
+// the scores and writes the next softmax, before the round's second barrier.
 template <int RREG, bool SEC, bool TRACE, int MAXT, int GMAX, bool TRAJ>
 __global__ __launch_bounds__(MAXT) void select_kernel(SelParams p) {
   constexpr bool GROUPED = GMAX > 1;

@@ -2,7 +2,10 @@
 pointer trajectory; stepprune_select_trajectory), against the oracle with the
 staged, teacher-forced protocol of tests/parity.py (check_trajectory for the
 sums, check_selection for the decisions), with and without the full rollout
-(SP_FULL_ROLLOUT), over every launch shape of the g = 1 kernels."""
+(SP_FULL_ROLLOUT): traced runs of the paper-shaped workloads and of histories
+past every tier.  The untraced kernels and the other launch shapes are in
+test_gpu_trajectory_shapes.py.
+"""
 import math
 
 import numpy as np
